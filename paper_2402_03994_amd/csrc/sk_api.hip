@@ -997,14 +997,34 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
                   run_affdq_apply(s, l, grads[l - l0], dtype, b0, bc, s->ws, out, acc, 2, st));
         }
         break;
-      case SK_QK:
+      case SK_QK: {
+        std::vector<int> rest;  // layers off the bf16 tiling: fp64 sums, many layers per launch
         for (int l = l0; l < l1; ++l) {
+          if (!qk_bf16_path(s->layers[l], dtype)) {
+            rest.push_back(l);
+            continue;
+          }
           SK_PROF(SK_PROF_QK_XB, bc * s->layers[l].n * esz,
                   launch_qk_apply(s, l, grads[l - l0], dtype, b0, bc, s->ws, 1, out, accumulate != 0, st));
           SK_PROF(SK_PROF_QK, bc * s->layers[l].da * s->layers[l].db * 4,
                   launch_qk_apply(s, l, grads[l - l0], dtype, b0, bc, s->ws, 2, out, accumulate != 0, st));
         }
+        for (size_t i = 0; i < rest.size();) {
+          const Qk64Group g = qk64_group(s, rest.data() + i, (int)(rest.size() - i), bc, s->ws_bytes);
+          const void *x[kQk64Tasks];
+          int64_t in_bytes = 0, out_bytes = 0;
+          for (int j = 0; j < g.n; ++j) {
+            const LayerDesc &ld = s->layers[g.layer[j]];
+            x[j] = grads[g.layer[j] - l0];
+            in_bytes += bc * ld.n * esz;
+            out_bytes += bc * ld.da * ld.db * 4;
+          }
+          SK_PROF(SK_PROF_QK_XB, in_bytes, launch_qk64_first(s, g, x, dtype, b0, bc, s->ws, st));
+          SK_PROF(SK_PROF_QK, out_bytes, launch_qk64_second(s, g, b0, bc, s->ws, out, accumulate != 0, st));
+          i += g.n;
+        }
         break;
+      }
     }
   }
   const hipError_t e = hipGetLastError();
@@ -1079,6 +1099,21 @@ int sketch_apply_T(sk_sketch *s, const float *z, int64_t batch, void *const *out
       run_afjlf_T(s, l0, l1, z, b0, bc, s->ws, s->ws_bytes / 4, out, out_dtype, theta0, st);
       continue;
     }
+    if (s->kind == SK_QK) {
+      for (int l = l0; l < l1;) {
+        const Qk64Group g = qk64_group_T(s, l, l1 - l, bc, s->ws_bytes);
+        int64_t bytes = 0;
+        for (int j = 0; j < g.n; ++j) {
+          const LayerDesc &ld = s->layers[l + j];
+          bytes += bc * ld.n * osz + (theta0 && theta0[l + j - l0] ? ld.n * 4 : 0) + bc * ld.da * ld.db * 4;
+        }
+        SK_PROF(SK_PROF_QK, bytes,
+                launch_qk64_T(s, g, z, b0, bc, s->ws, out + (l - l0), out_dtype, theta0 ? theta0 + (l - l0) : nullptr,
+                              st));
+        l += g.n;
+      }
+      continue;
+    }
     for (int l = l0; l < l1; ++l) {
       const LayerDesc &ld = s->layers[l];
       void *o = out[l - l0];
@@ -1142,9 +1177,7 @@ int sketch_apply_T(sk_sketch *s, const float *z, int64_t batch, void *const *out
         case SK_AFFDQ:
           SK_PROF(SK_PROF_QH_T, obytes, run_affdq_apply_T(s, l, z, b0, bc, s->ws, o, out_dtype, th, st));
           break;
-        case SK_QK:
-          SK_PROF(SK_PROF_QK, obytes + bc * ld.da * ld.db * 4,
-                  launch_qk_apply_T(s, l, z, b0, bc, s->ws, o, out_dtype, th, st));
+        case SK_QK:  // grouped above
           break;
       }
     }

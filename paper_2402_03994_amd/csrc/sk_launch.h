@@ -238,8 +238,57 @@ void launch_qk_factors(const sk_sketch *s, hipStream_t st);
 // stages: bit 0 = T = X B^T (reads the gradients), bit 1 = out (+)= A T
 void launch_qk_apply(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc,
                      float *t_ws, int stages, float *out, bool accumulate, hipStream_t st);
-int64_t qk_workspace_elems(const sk_sketch *s, int layer, int64_t bc);
-void launch_qk_apply_T(const sk_sketch *s, int layer, const float *z, int64_t b_begin, int64_t bc, float *t_ws,
-                       void *out, int out_dtype, const float *theta0, hipStream_t st);
+// Does the layer take the bf16 matrix-core contractions of launch_qk_apply?  (Else: the fp64-sum ones below.)
+bool qk_bf16_path(const LayerDesc &ld, int dtype);
+
+// fp64-sum contractions (sk_qk64.hip): tasks of up to kQk64Tasks layers per launch, by value in the kernel
+// arguments (under 4 KB).
+constexpr int kQk64Tasks = 32;
+struct Qk64Dot {  // out[p][q] = sum_k P[p][k] Q[q][k] per vector, rows of K entries
+  const float *p;
+  const void *q;
+  float *o;
+  double *part;  // partial sums [k range][vector][np][nq] in place of o, or NULL
+  int64_t pvs, qvs, ovs;  // strides between vectors
+  int64_t K, klen;        // k ranges of klen (a multiple of 16)
+  int32_t ldo, np, nq, nk, nbp, nbq, tp;
+};
+struct Qk64DotArgs {
+  Qk64Dot t[kQk64Tasks];
+  uint32_t blk0[kQk64Tasks];
+  int64_t nv;
+  int32_t n, accumulate;
+};
+struct Qk64Outer {  // out[i][j] = sum_k P(k, i) Q[k][j] (+ theta), P(k, i) = p[k psk + i psi]
+  const float *p;
+  const void *q;
+  void *o;
+  const float *theta;
+  int64_t pvs, psk, psi, qvs, ovs, K;
+  int32_t M, N, nbm, nbn, tm;
+};
+struct Qk64OuterArgs {
+  Qk64Outer t[kQk64Tasks];
+  uint32_t blk0[kQk64Tasks];
+  int64_t nv;
+  int32_t n, out_bf16;
+};
+struct Qk64Group {  // layers of one set of launches and their places in the workspace (in floats)
+  int32_t n;
+  int32_t layer[kQk64Tasks];
+  bool afirst[kQk64Tasks];
+  int64_t t_off[kQk64Tasks], part_off[kQk64Tasks], klen[kQk64Tasks];
+  int32_t nk[kQk64Tasks];
+};
+// The next layers of the list whose intermediates for bc vectors fit the workspace together (at least one).
+Qk64Group qk64_group(const sk_sketch *s, const int *layers, int count, int64_t bc, int64_t ws_bytes);
+Qk64Group qk64_group_T(const sk_sketch *s, int l0, int count, int64_t bc, int64_t ws_bytes);
+// x, out, theta0: one pointer per layer of the group.
+void launch_qk64_first(const sk_sketch *s, const Qk64Group &g, const void *const *x, int dtype, int64_t b_begin,
+                       int64_t bc, float *ws, hipStream_t st);
+void launch_qk64_second(const sk_sketch *s, const Qk64Group &g, int64_t b_begin, int64_t bc, float *ws, float *out,
+                        bool accumulate, hipStream_t st);
+void launch_qk64_T(const sk_sketch *s, const Qk64Group &g, const float *z, int64_t b_begin, int64_t bc, float *ws,
+                   void *const *out, int out_dtype, const void *const *theta0, hipStream_t st);
 
 }  // namespace sk

@@ -5,8 +5,9 @@
 // in fp32.  A and B are kept in fp32 and, for the bf16 matrix-core
 // contractions of bf16 inputs, also as two bf16 terms, hi = bf16(F) and
 // lo = bf16(F - hi) (both rounded to nearest even), so that X B^T =
-// X hi^T + X lo^T sees B to 16 mantissa bits.  fp32 inputs and the transpose
-// multiply by the fp32 factors.  Products accumulate in fp32.
+// X hi^T + X lo^T sees B to 16 mantissa bits.  Products accumulate in fp32.
+// fp32 inputs, shapes off the tiling below and the transpose multiply by the
+// fp32 factors with fp64 sums (sk_qk64.hip).
 #include <algorithm>
 
 #include "sk_launch.h"
@@ -55,31 +56,6 @@ void launch_qk_factors(const sk_sketch *s, hipStream_t st) {
                        (float)(1.0 / sqrt((double)ld.db)), s->key);
   }
   (void)hipGetLastError();
-}
-
-int64_t qk_workspace_elems(const sk_sketch *s, int layer, int64_t bc) {
-  const LayerDesc &ld = s->layers[layer];
-  return bc * std::max((int64_t)ld.m * ld.db, (int64_t)ld.da * ld.nc);
-}
-
-// T[v][i][c] = sum_j X[v][i][j] B[c][j] with the fp32 B (inputs that the
-// matrix-core path does not take: fp32, or shapes off its tiling).  These
-// one-thread-per-output loops sum in fp64 and round once, so their error does
-// not grow with the contraction length.
-template <bool BF16>
-__global__ void k_qk_xbt(const void *__restrict__ x, const float *__restrict__ B, int m, int n, int db,
-                         int64_t b_begin, float *__restrict__ t) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t v = blockIdx.y;
-  if (e >= (int64_t)m * db) return;
-  const int64_t i = e / db, c = e - (e / db) * db;
-  const int64_t xo = ((b_begin + v) * m + i) * (int64_t)n;
-  double acc = 0.0;
-  for (int64_t j = 0; j < n; ++j) {
-    const float xv = BF16 ? qk_bf2f(((const uint16_t *)x)[xo + j]) : ((const float *)x)[xo + j];
-    acc = fma((double)xv, (double)B[c * n + j], acc);
-  }
-  t[(v * m + i) * db + c] = (float)acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -464,18 +440,7 @@ bool qk_mfma_ok(const LayerDesc &ld, int dtype) {
   return dtype == SK_BF16 && ld.nc % 128 == 0 && ld.m % 16 == 0 && ld.da % 16 == 0 && ld.db % 16 == 0 && ld.db <= 128;
 }
 
-// Y[v][a][c] = sum_i A[a][i] T[v][i][c]
-__global__ void k_qk_at(const float *__restrict__ A, const float *__restrict__ t, int m, int da, int db,
-                        int64_t D, int64_t col, int64_t b_begin, float *__restrict__ out, int accumulate) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t v = blockIdx.y;
-  if (e >= (int64_t)da * db) return;
-  const int64_t a = e / db, c = e - (e / db) * db;
-  double acc = 0.0;
-  for (int64_t i = 0; i < m; ++i) acc = fma((double)A[a * m + i], (double)t[(v * m + i) * db + c], acc);
-  float *o = out + (b_begin + v) * D + col + e;
-  *o = accumulate ? *o + (float)acc : (float)acc;
-}
+bool qk_bf16_path(const LayerDesc &ld, int dtype) { return qk_afirst_ok(ld, dtype) || qk_mfma_ok(ld, dtype); }
 
 void launch_qk_apply(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc,
                      float *t_ws, int stages, float *out, bool accumulate, hipStream_t st) {
@@ -514,84 +479,25 @@ void launch_qk_apply(const sk_sketch *s, int layer, const void *x, int dtype, in
     (void)hipGetLastError();
     return;
   }
-  if (qk_mfma_ok(ld, dtype)) {
-    const int64_t rows = bc * (int64_t)ld.m;
-    dim3 g1((unsigned)((rows + kQkRows - 1) / kQkRows));
-    if (stages & 1) {
-#define SK_S1(NT)                                                                                              \
-  case NT:                                                                                                     \
-    hipLaunchKernelGGL(k_qk_s1<NT>, g1, dim3(256), 0, st, (const uint16_t *)x, B, Blo, (int64_t)ld.m,           \
-                       (int64_t)ld.nc,                                                                         \
-                       b_begin, rows, t_ws);                                                                   \
-    break;
-    switch (ld.db / 16) {
-      SK_S1(1) SK_S1(2) SK_S1(3) SK_S1(4) SK_S1(5) SK_S1(6) SK_S1(7) SK_S1(8)
-      default: break;
-    }
-#undef SK_S1
-    }
-    if (stages & 2) {
-      launch_qk_s2(A, 0, t_ws, (int64_t)ld.db * ld.m, (int64_t)ld.m, ld.da, ld.db, s->D, ld.qk_col, b_begin, bc, out,
-                   accumulate, st);
-    }
-    (void)hipGetLastError();
-    return;
-  }
+  const int64_t rows = bc * (int64_t)ld.m;
+  dim3 g1((unsigned)((rows + kQkRows - 1) / kQkRows));
   if (stages & 1) {
-    dim3 g1((unsigned)(((int64_t)ld.m * ld.db + 255) / 256), (unsigned)bc);
-    const float *Bf = s->d_qkbf + ld.fb_off;
-    if (dtype == SK_BF16)
-      hipLaunchKernelGGL(k_qk_xbt<true>, g1, dim3(256), 0, st, x, Bf, ld.m, ld.nc, ld.db, b_begin, t_ws);
-    else
-      hipLaunchKernelGGL(k_qk_xbt<false>, g1, dim3(256), 0, st, x, Bf, ld.m, ld.nc, ld.db, b_begin, t_ws);
+#define SK_S1(NT)                                                                                              \
+case NT:                                                                                                     \
+  hipLaunchKernelGGL(k_qk_s1<NT>, g1, dim3(256), 0, st, (const uint16_t *)x, B, Blo, (int64_t)ld.m,           \
+                     (int64_t)ld.nc,                                                                         \
+                     b_begin, rows, t_ws);                                                                   \
+  break;
+  switch (ld.db / 16) {
+    SK_S1(1) SK_S1(2) SK_S1(3) SK_S1(4) SK_S1(5) SK_S1(6) SK_S1(7) SK_S1(8)
+    default: break;
+  }
+#undef SK_S1
   }
   if (stages & 2) {
-    dim3 g2((unsigned)(((int64_t)ld.da * ld.db + 255) / 256), (unsigned)bc);
-    hipLaunchKernelGGL(k_qk_at, g2, dim3(256), 0, st, A, t_ws, ld.m, ld.da, ld.db, s->D, ld.qk_col, b_begin, out,
-                       (int)accumulate);
+    launch_qk_s2(A, 0, t_ws, (int64_t)ld.db * ld.m, (int64_t)ld.m, ld.da, ld.db, s->D, ld.qk_col, b_begin, bc, out,
+                 accumulate, st);
   }
-  (void)hipGetLastError();
-}
-
-// U[v][i][c] = sum_a A[a][i] Z[v][a][c]
-__global__ void k_qk_atz(const float *__restrict__ A, const float *__restrict__ z, int m, int da, int db, int64_t D,
-                         int64_t col, int64_t b_begin, float *__restrict__ u) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t v = blockIdx.y;
-  if (e >= (int64_t)m * db) return;
-  const int64_t i = e / db, c = e - (e / db) * db;
-  double acc = 0.0;
-  for (int64_t a = 0; a < da; ++a) acc = fma((double)A[a * m + i], (double)z[(b_begin + v) * D + col + a * db + c], acc);
-  u[(v * m + i) * db + c] = (float)acc;
-}
-
-// X'[v][i][j] = sum_c U[v][i][c] B[c][j] (+ theta0), fp32 B
-__global__ void k_qk_ub(const float *__restrict__ B, const float *__restrict__ u, int m, int n, int db,
-                        int64_t b_begin, void *__restrict__ out, int out_dtype, const float *__restrict__ theta0) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t v = blockIdx.y;
-  if (e >= (int64_t)m * n) return;
-  const int64_t i = e / n, j = e - (e / n) * n;
-  double acc = 0.0;
-  for (int64_t c = 0; c < db; ++c) acc = fma((double)u[(v * m + i) * db + c], (double)B[c * n + j], acc);
-  if (theta0) acc += theta0[e];
-  const float r = (float)acc;
-  const int64_t o = (b_begin + v) * (int64_t)m * n + e;
-  if (out_dtype == SK_BF16)
-    ((uint16_t *)out)[o] = qk_f2bf(r);
-  else
-    ((float *)out)[o] = r;
-}
-
-void launch_qk_apply_T(const sk_sketch *s, int layer, const float *z, int64_t b_begin, int64_t bc, float *t_ws,
-                       void *out, int out_dtype, const float *theta0, hipStream_t st) {
-  const LayerDesc &ld = s->layers[layer];
-  const float *A = s->d_qka + ld.fa_off;
-  const float *Bf = s->d_qkbf + ld.fb_off;
-  dim3 g1((unsigned)(((int64_t)ld.m * ld.db + 255) / 256), (unsigned)bc);
-  hipLaunchKernelGGL(k_qk_atz, g1, dim3(256), 0, st, A, z, ld.m, ld.da, ld.db, s->D, ld.qk_col, b_begin, t_ws);
-  dim3 g2((unsigned)(((int64_t)ld.m * ld.nc + 255) / 256), (unsigned)bc);
-  hipLaunchKernelGGL(k_qk_ub, g2, dim3(256), 0, st, Bf, t_ws, ld.m, ld.nc, ld.db, b_begin, out, out_dtype, theta0);
   (void)hipGetLastError();
 }
 
