@@ -730,28 +730,23 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
       case SK_AFJL: {
         // fold launches of at most kMaxPtrs layers, then one tail over all layers
         const int it_base = s->layers[l0].item_off;
-        int64_t in_bytes = 0;
+        const int split = afjl_fold_split(s, l0, l1, bc, std::min(bc, batch - b0));
         for (int g0 = l0; g0 < l1; g0 += kMaxPtrs) {
           const int g1 = std::min(l1, g0 + kMaxPtrs);
           PtrPack pp{};
-          bool vec = true;
           int64_t gb = 0;
           for (int l = g0; l < g1; ++l) {
             pp.p[l - g0] = grads[l - l0];
             gb += bc * s->layers[l].n * esz;
-            // vector loads: 4 fp32 or 8 bf16 elements (16 bytes) per thread
-            if ((s->layers[l].n & (dtype == SK_BF16 ? 7 : 3)) || ((uintptr_t)grads[l - l0] & 15)) vec = false;
           }
-          in_bytes += gb;
           const int it0 = s->layers[g0].item_off;
           const int it1 = s->layers[g1 - 1].item_off + s->layers[g1 - 1].n_items;
-          float *part = s->ws + (int64_t)(it0 - it_base) * bc * s->Lw;
+          float *part = s->ws + (int64_t)(it0 - it_base) * split * bc * s->Lw;
           SK_PROF(SK_PROF_AFJL_FOLD, gb,
-                  launch_afjl_fold(s, pp, g0, dtype, vec, batch, b0, bc, it0, it1, part, st));
+                  launch_afjl_fold(s, pp, g0, dtype, batch, b0, bc, it0, it1, split, part, st));
         }
         SK_PROF(SK_PROF_AFJL_TAIL, bc * s->D * 4,
-                launch_afjl_tail(s, l0, l1, it_base, s->ws, bc, b0, batch, out, accumulate != 0, st));
-        (void)in_bytes;
+                launch_afjl_tail(s, l0, l1, it_base, split, s->ws, bc, b0, batch, out, accumulate != 0, st));
         break;
       }
       case SK_AFFD: {

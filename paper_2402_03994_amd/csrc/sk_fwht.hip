@@ -123,32 +123,25 @@ void launch_fill_zero(float *p, int64_t n, hipStream_t st) {
 // kernel applies H_L to each destination row, the tail kernel H_R, G and the
 // sum over layers.  For D < L the row is folded once more to D columns.
 // ===========================================================================
-// Up to CPT consecutive input elements starting at element e (missing -> 0).
-template <int CPT, bool BF16, bool VEC>
-__device__ __forceinline__ void load_cols(const void *x, int64_t e, int64_t lim, float v[CPT]) {
-  if (CPT == 8 && BF16 && VEC && lim >= 8) {
-    const uint4 u = *(const uint4 *)((const uint16_t *)x + e);
-    v[0] = __uint_as_float(u.x << 16);
-    v[1] = __uint_as_float(u.x & 0xFFFF0000u);
-    v[2] = __uint_as_float(u.y << 16);
-    v[3] = __uint_as_float(u.y & 0xFFFF0000u);
-    v[4] = __uint_as_float(u.z << 16);
-    v[5] = __uint_as_float(u.z & 0xFFFF0000u);
-    v[6] = __uint_as_float(u.w << 16);
-    v[7] = __uint_as_float(u.w & 0xFFFF0000u);
-    return;
-  }
-#pragma unroll
-  for (int q = 0; q < CPT; q += 4) load4<BF16, VEC>(x, e + q, lim - q, v + q);
-}
-
-// CPT (4 fp32 or up to 8 bf16) consecutive elements from element e as their raw
-// bit patterns in 16 bytes; elements at or past lim read as zero.
-template <int CPT, bool BF16, bool VEC>
+// CPT (4 fp32 or 8 bf16) consecutive elements from element e as their raw bit
+// patterns in 16 bytes; elements at or past lim read as zero.  The load is
+// typed with the element's alignment: vectors of a batch and views of a flat
+// gradient start anywhere, and one 16-byte access at any address costs at most
+// one line more than an aligned one, while element loads for layers whose size
+// is not a multiple of the piece ran at a quarter of the rate (four loads and
+// four waits; one 2-entry bias put all layers of a call on them).
+template <bool BF16>
 __device__ __forceinline__ uint4 load_raw16(const void *x, int64_t e, int64_t lim) {
-  if (VEC && lim >= CPT && (BF16 ? CPT == 8 : CPT == 4)) {
-    // each input element is read once
-    return ld_nt16(BF16 ? (const void *)((const uint16_t *)x + e) : (const void *)((const float *)x + e));
+  typedef uint32_t u4f __attribute__((ext_vector_type(4), aligned(4)));
+  typedef uint32_t u4h __attribute__((ext_vector_type(4), aligned(2)));
+  constexpr int CPT = BF16 ? 8 : 4;
+  if (lim >= CPT) {  // each input element is read once
+    if (BF16) {
+      const u4h r = __builtin_nontemporal_load((const u4h *)((const uint16_t *)x + e));
+      return make_uint4(r.x, r.y, r.z, r.w);
+    }
+    const u4f r = __builtin_nontemporal_load((const u4f *)((const float *)x + e));
+    return make_uint4(r.x, r.y, r.z, r.w);
   }
   uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -170,23 +163,37 @@ __device__ __forceinline__ float raw16_value(const uint4 &r, int q) {
   return BF16 ? __uint_as_float((q & 1) ? (w & 0xFFFF0000u) : (w << 16)) : __uint_as_float(w);
 }
 
+// Share z of S of an item's source rows.  Calls that would leave the chip idle
+// (a classification head is 8 items of up to 256 rows in a row: 80 us on 8
+// workgroups for 2.4 MB) split every item over S workgroups; each share writes
+// a partial of its own and the tail adds them in order.
+__device__ __forceinline__ FoldItem fold_share(FoldItem it, int z, int S) {
+  const int len = (it.t1 - it.t0 + S - 1) / S;
+  const int a = it.t0 + z * len;
+  const int b = a + len < it.t1 ? a + len : it.t1;
+  it.t0 = a < b ? a : b;
+  it.t1 = b;
+  return it;
+}
+
 // Fold kernel.  Each thread owns CPT consecutive columns of a row; when a row
 // needs fewer than 256 threads, NGR = 256 / (L / CPT) row groups take
 // interleaved rows and their sums are combined in LDS in group order.  The
 // item's source rows are resolved into LDS first, and the loads of a group's
 // next row are issued before the current one is added.
-template <int BT, int CPT, bool BF16, bool VEC>
+template <int BT, bool BF16>
 __global__ __launch_bounds__(256) void k_afjl_fold(const FoldItem *__restrict__ items,
                                                    const LayerDesc *__restrict__ layers,
                                                    const uint16_t *__restrict__ ptab, PtrPack ptrs, int first_layer,
                                                    int64_t batch, int64_t b_begin, int64_t bc, int item_begin, int R,
                                                    int Lw, float *__restrict__ part, Key key) {
+  constexpr int CPT = BF16 ? 8 : 4;
   using LF = Lds1024<BT>;
   __shared__ __align__(16) float s_raw[LF::kFloats > BT * 1024 ? LF::kFloats : BT * 1024];
   static_assert(kFoldRowsPerItem <= 256, "one thread per source row of an item");
   __shared__ int32_t srow[kFoldRowsPerItem];
   float(*s)[1024] = reinterpret_cast<float(*)[1024]>(s_raw);
-  const FoldItem it = items[item_begin + blockIdx.x];
+  const FoldItem it = fold_share(items[item_begin + blockIdx.x], blockIdx.z, gridDim.z);
   const LayerDesc &ld = layers[it.layer];
   const int64_t n = ld.n;
   const int L = ld.L;
@@ -234,7 +241,7 @@ __global__ __launch_bounds__(256) void k_afjl_fold(const FoldItem *__restrict__ 
 #pragma unroll
       for (int b = 0; b < BT; ++b) {
         v[b] = make_uint4(0u, 0u, 0u, 0u);
-        if (jn >= 0 && b < nb) v[b] = load_raw16<CPT, BF16, VEC>(xp, (b_begin + bt0 + b) * n + jn, n - jn);
+        if (jn >= 0 && b < nb) v[b] = load_raw16<BF16>(xp, (b_begin + bt0 + b) * n + jn, n - jn);
       }
     };
     fetch(grp);
@@ -260,7 +267,7 @@ __global__ __launch_bounds__(256) void k_afjl_fold(const FoldItem *__restrict__ 
 #pragma unroll
     for (int q = 0; q < CPT; ++q) pc[q] = fwd_k[col0 + q];
   }
-  const int64_t slot = blockIdx.x;
+  const int64_t slot = (int64_t)blockIdx.x * gridDim.z + blockIdx.z;
   if (L == 1024 && Lw == 1024) {
     // row groups add in order, then H_L of the BT rows in a conflict-free LDS block
     for (int gi = 0; gi < ngr; ++gi) {
@@ -329,19 +336,20 @@ __global__ __launch_bounds__(256) void k_afjl_fold(const FoldItem *__restrict__ 
 // built first, one Philox block per 128 coordinates (8 per source row) into
 // LDS, and each row group keeps PF rows of 16-byte loads in flight (one
 // vector gives a workgroup too little work to hide the latency otherwise).
-template <int CPT, bool BF16, bool VEC>
+template <bool BF16>
 __global__ __launch_bounds__(256) void k_afjl_fold1(const FoldItem *__restrict__ items,
                                                     const LayerDesc *__restrict__ layers,
                                                     const uint16_t *__restrict__ ptab, PtrPack ptrs, int first_layer,
                                                     int64_t b_row, int64_t bc, int64_t slot_row, int item_begin, int R,
                                                     float *__restrict__ part, Key key) {
   constexpr int PF = 4;
+  constexpr int CPT = BF16 ? 8 : 4;
   constexpr int TPR = 1024 / CPT;  // threads per row
   constexpr int NGR = 256 / TPR;   // row groups
-  __shared__ float s[1024];
+  __shared__ float s[p16_floats(1024)];
   __shared__ int32_t srow[kFoldRowsPerItem];
   __shared__ __align__(16) uint32_t sgn[kFoldRowsPerItem * 32];
-  const FoldItem it = items[item_begin + blockIdx.x];
+  const FoldItem it = fold_share(items[item_begin + blockIdx.x], blockIdx.z, gridDim.z);
   const LayerDesc &ld = layers[it.layer];
   const int64_t n = ld.n;
   const int tid = threadIdx.x;
@@ -386,7 +394,7 @@ __global__ __launch_bounds__(256) void k_afjl_fold1(const FoldItem *__restrict__
     jn = h >= 0 ? (int64_t)h * 1024 + col0 : -1;
     if (jn >= n) jn = -1;
     v = make_uint4(0u, 0u, 0u, 0u);
-    if (jn >= 0) v = load_raw16<CPT, BF16, VEC>(xp, xrow + jn, n - jn);
+    if (jn >= 0) v = load_raw16<BF16>(xp, xrow + jn, n - jn);
   };
 #pragma unroll
   for (int p = 0; p < PF; ++p) fetch(grp + p * NGR, ring[p], jr[p]);
@@ -408,7 +416,7 @@ __global__ __launch_bounds__(256) void k_afjl_fold1(const FoldItem *__restrict__
   const uint16_t *fwd_k = ptab + ld.poff[0][0][ld.K - 1];
   int pc[CPT];
 #pragma unroll
-  for (int q = 0; q < CPT; ++q) pc[q] = fwd_k[col0 + q];
+  for (int q = 0; q < CPT; ++q) pc[q] = p16(fwd_k[col0 + q]);
   for (int gi = 0; gi < NGR; ++gi) {
     if (grp == gi) {
 #pragma unroll
@@ -416,17 +424,39 @@ __global__ __launch_bounds__(256) void k_afjl_fold1(const FoldItem *__restrict__
     }
     __syncthreads();
   }
-  lds_fwht(s, 10, 0);
-  const int64_t slot = blockIdx.x;
+  lds_fwht_regs(s, 10, 0);
+  const int64_t slot = (int64_t)blockIdx.x * gridDim.z + blockIdx.z;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int c = tid + 256 * k;
-    part[(slot * bc + slot_row) * 1024 + c] = s[c] * (1.0f / 32.0f);
+    part[(slot * bc + slot_row) * 1024 + c] = s[p16(c)] * (1.0f / 32.0f);
   }
 }
 
-void launch_afjl_fold(const sk_sketch *s, const PtrPack &ptrs, int first_layer, int dtype, bool vec, int64_t batch,
-                      int64_t b_begin, int64_t bc, int item_begin, int item_end, float *part, hipStream_t st) {
+// Workgroups per fold item: the fold's grid is brought to at most 1024
+// workgroups (four per CU, what the kernels' LDS allows) while every share
+// keeps 8 or more rows; partial sums beyond the workspace and the tails for
+// R > 64 (whose items are many and short already) take none.
+int afjl_fold_split(const sk_sketch *s, int l0, int l1, int64_t bc, int64_t rows) {
+  if (s->R > 64) return 1;
+  const int64_t items = s->layers[l1 - 1].item_off + s->layers[l1 - 1].n_items - s->layers[l0].item_off;
+  int64_t most = 0;  // rows of the longest item
+  for (int l = l0; l < l1; ++l) {
+    const LayerDesc &ld = s->layers[l];
+    const int64_t t = s->R == 1 ? ld.rows_live : (ld.rows_live + ld.dk1 - 1) / ld.dk1 * (ld.dk1 / s->R);
+    most = std::max(most, std::min<int64_t>(t, kFoldRowsPerItem));
+  }
+  const int64_t blocks = items * (rows == 1 ? 1 : (rows + 7) / 8);
+  int S = 1;
+  while (blocks * S * 2 <= 1024 && most >= 8 * S * 2 &&
+         bc * (items * S * 2 * s->Lw + (int64_t)kTailGroups * s->D) * 4 <= s->ws_bytes)
+    S *= 2;
+  return S;
+}
+
+void launch_afjl_fold(const sk_sketch *s, const PtrPack &ptrs, int first_layer, int dtype, int64_t batch,
+                      int64_t b_begin, int64_t bc, int item_begin, int item_end, int split, float *part,
+                      hipStream_t st) {
   constexpr int BT = 8;
   const int nitems = item_end - item_begin;
   if (nitems <= 0) return;
@@ -434,28 +464,24 @@ void launch_afjl_fold(const sk_sketch *s, const PtrPack &ptrs, int first_layer, 
   bool one = rows == 1 && s->Lw == 1024;
   for (int i = item_begin; i < item_end && one; ++i) one = s->layers[s->items[i].layer].L == 1024;
   if (one) {
-#define SK_FOLD1(CPT, BF, VE)                                                                                        \
-  hipLaunchKernelGGL((k_afjl_fold1<CPT, BF, VE>), dim3((unsigned)nitems), dim3(256), 0, st, s->d_items, s->d_layers, \
-                     s->d_ptab, ptrs, first_layer, b_begin, bc, (int64_t)0, item_begin, s->R, part, s->key)
-    if (dtype == SK_BF16) {
-      if (vec) SK_FOLD1(8, true, true); else SK_FOLD1(4, true, false);
-    } else {
-      if (vec) SK_FOLD1(4, false, true); else SK_FOLD1(4, false, false);
-    }
-#undef SK_FOLD1
+    const dim3 grid((unsigned)nitems, 1u, (unsigned)split);
+    if (dtype == SK_BF16)
+      hipLaunchKernelGGL(k_afjl_fold1<true>, grid, dim3(256), 0, st, s->d_items, s->d_layers, s->d_ptab, ptrs,
+                         first_layer, b_begin, bc, (int64_t)0, item_begin, s->R, part, s->key);
+    else
+      hipLaunchKernelGGL(k_afjl_fold1<false>, grid, dim3(256), 0, st, s->d_items, s->d_layers, s->d_ptab, ptrs,
+                         first_layer, b_begin, bc, (int64_t)0, item_begin, s->R, part, s->key);
     SK_CHECK_LAUNCH();
     return;
   }
-  dim3 grid((unsigned)nitems, (unsigned)((rows + BT - 1) / BT));
-#define SK_FOLD(CPT, BF, VE)                                                                                       \
-  hipLaunchKernelGGL((k_afjl_fold<BT, CPT, BF, VE>), grid, dim3(256), 0, st, s->d_items, s->d_layers, s->d_ptab,   \
-                     ptrs, first_layer, batch, b_begin, bc, item_begin, s->R, s->Lw, part, s->key)
-  if (dtype == SK_BF16) {
-    if (vec) SK_FOLD(8, true, true); else SK_FOLD(4, true, false);
-  } else {
-    if (vec) SK_FOLD(4, false, true); else SK_FOLD(4, false, false);
-  }
-#undef SK_FOLD
+  const dim3 grid((unsigned)nitems, (unsigned)((rows + BT - 1) / BT), (unsigned)split);
+  batch = b_begin + rows;  // the last tile ends with this call's vectors, not with the batch
+  if (dtype == SK_BF16)
+    hipLaunchKernelGGL((k_afjl_fold<BT, true>), grid, dim3(256), 0, st, s->d_items, s->d_layers, s->d_ptab, ptrs,
+                       first_layer, batch, b_begin, bc, item_begin, s->R, s->Lw, part, s->key);
+  else
+    hipLaunchKernelGGL((k_afjl_fold<BT, false>), grid, dim3(256), 0, st, s->d_items, s->d_layers, s->d_ptab, ptrs,
+                       first_layer, batch, b_begin, bc, item_begin, s->R, s->Lw, part, s->key);
   SK_CHECK_LAUNCH();
 }
 
@@ -526,11 +552,14 @@ __global__ __launch_bounds__(256) void k_afjl_tail(const LayerDesc *__restrict__
 // most one item per row the J loads go out together; otherwise chunk k of
 // every row is added in turn, the row records being re-read for each chunk
 // rather than held in registers.
+// Split items (S shares each): share z of item i is partial i S + z, and part
+// zi of zg sums an even range of every row's shares.
 template <int J>
 __device__ __forceinline__ void tail_gather(int maxch, const int2 *rs, const int32_t *rf, __amdgpu_buffer_rsrc_t pr,
-                                            uint32_t stride, uint32_t voff0, int item0, float (&v)[J]) {
+                                            uint32_t stride, uint32_t voff0, int item0, int S, int zi, int zg,
+                                            float (&v)[J]) {
   constexpr uint32_t kNone = 0x80000000u;  // beyond the resource (< 2^31 bytes)
-  if (maxch <= 1) {
+  if (maxch * S <= 1) {
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       const int f = rf[j];
@@ -541,14 +570,35 @@ __device__ __forceinline__ void tail_gather(int maxch, const int2 *rs, const int
   }
 #pragma unroll
   for (int j = 0; j < J; ++j) v[j] = 0.0f;
-  for (int k = 0; k < maxch; ++k) {
+  if constexpr (J < 16) {  // few rows: 16 / J partials of each in flight together
+    constexpr int KU = 16 / J;
+    const int len = (maxch * S + zg - 1) / zg, kend = (zi + 1) * len;
+    for (int k = zi * len; k < kend; k += KU) {
+      float p[KU][J];
+#pragma unroll
+      for (int u = 0; u < KU; ++u)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const int2 q = rs[j];
+          const uint32_t off = k + u < kend && k + u < q.y * S ? (uint32_t)((q.x - item0) * S + k + u) * stride + voff0 : kNone;
+          p[u][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, (int)off, 0, 0));
+        }
+#pragma unroll
+      for (int u = 0; u < KU; ++u)
+#pragma unroll
+        for (int j = 0; j < J; ++j) v[j] += p[u][j];
+    }
+    return;
+  }
+  const int len = (maxch * S + zg - 1) / zg;
+  for (int k = zi * len; k < (zi + 1) * len; ++k) {
 #pragma unroll
     for (int j0 = 0; j0 < J; j0 += 16) {
       asm volatile("" ::: "memory");  // re-read the row records
 #pragma unroll
       for (int j = j0; j < j0 + 16 && j < J; ++j) {
         const int2 q = rs[j];
-        const uint32_t off = k < q.y ? (uint32_t)(q.x + k - item0) * stride + voff0 : kNone;
+        const uint32_t off = k < q.y * S ? (uint32_t)((q.x - item0) * S + k) * stride + voff0 : kNone;
         v[j] += __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, (int)off, 0, 0));
       }
     }
@@ -558,8 +608,9 @@ __device__ __forceinline__ void tail_gather(int maxch, const int2 *rs, const int
 // The partials of layer ld as a buffer resource (the callers keep each
 // layer's partials below 2^31 bytes).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tail_part_rsrc(const LayerDesc &ld, const float *part, int item_begin,
-                                                                 int64_t bc, int Lw) {
-  return buf_rsrc(part + (int64_t)(ld.item_off - item_begin) * bc * Lw, (uint32_t)((int64_t)ld.n_items * bc * Lw * 4));
+                                                                 int64_t bc, int Lw, int S) {
+  return buf_rsrc(part + (int64_t)(ld.item_off - item_begin) * S * bc * Lw,
+                  (uint32_t)((int64_t)ld.n_items * S * bc * Lw * 4));
 }
 
 // Tail for R <= 64: the R values of a (vector, column) stay in registers
@@ -574,8 +625,8 @@ __global__ __launch_bounds__(256, 4) void k_afjl_tail_reg(const LayerDesc *__res
                                                        const int2 *__restrict__ rslot,
                                                        const int32_t *__restrict__ rfirst, const float *__restrict__ part,
                                                        const float *__restrict__ gtab, TailGroups grp,
-                                                       int item_begin, int Lw, int64_t D, int64_t bc, int64_t b_begin,
-                                                       int64_t batch, float *__restrict__ ysum) {
+                                                       int item_begin, int S, int zg, int Lw, int64_t D, int64_t bc,
+                                                       int64_t b_begin, int64_t batch, float *__restrict__ ysum) {
   constexpr int H = R > 32 ? 2 : 1, J = R / H;
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   int c, h;
@@ -592,7 +643,8 @@ __global__ __launch_bounds__(256, 4) void k_afjl_tail_reg(const LayerDesc *__res
     h = (int)((threadIdx.x >> 5) & 1);
   }
   if (bl >= bc || b_begin + bl >= batch) return;
-  const int l_begin = grp.bound[blockIdx.y], l_end = grp.bound[blockIdx.y + 1];
+  const int lgrp = blockIdx.y / zg, zi = blockIdx.y - lgrp * zg;
+  const int l_begin = grp.bound[lgrp], l_end = grp.bound[lgrp + 1];
   float acc[J];
 #pragma unroll
   for (int j = 0; j < J; ++j) acc[j] = 0.0f;
@@ -604,8 +656,8 @@ __global__ __launch_bounds__(256, 4) void k_afjl_tail_reg(const LayerDesc *__res
     const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gtab + (int64_t)l * D, (uint32_t)(D * 4));
     const int goff = (h * J * Lw + c) * 4;
     float v[J], gv[J];
-    tail_gather<J>(ld.rmaxch, rs, rf, tail_part_rsrc(ld, part, item_begin, bc, Lw), (uint32_t)(bc * Lw * 4),
-                   (uint32_t)((bl * Lw + c) * 4), ld.item_off, v);
+    tail_gather<J>(ld.rmaxch, rs, rf, tail_part_rsrc(ld, part, item_begin, bc, Lw, S), (uint32_t)(bc * Lw * 4),
+                   (uint32_t)((bl * Lw + c) * 4), ld.item_off, S, zi, zg, v);
     // the G loads go out while the partials are in flight
 #pragma unroll
     for (int j = 0; j < J; ++j) gv[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, goff, j * Lw * 4, 0));
@@ -653,8 +705,8 @@ __global__ __launch_bounds__(1024) void k_afjl_tail_1024w(const LayerDesc *__res
     const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gtab + (int64_t)l * D, (uint32_t)(D * 4));
     const int goff = (hi * 1024 + c0 + c) * 4;
     const LayerDesc &ld = layers[l];
-    tail_gather<32>(ld.rmaxch, rs + hi * 32, rfirst + ld.rslot_off + hi * 32, tail_part_rsrc(ld, part, item_begin, bc, 1024),
-                    (uint32_t)(bc * 1024 * 4), (uint32_t)((bl * 1024 + c0 + c) * 4), ld.item_off, v);
+    tail_gather<32>(ld.rmaxch, rs + hi * 32, rfirst + ld.rslot_off + hi * 32, tail_part_rsrc(ld, part, item_begin, bc, 1024, 1),
+                    (uint32_t)(bc * 1024 * 4), (uint32_t)((bl * 1024 + c0 + c) * 4), ld.item_off, 1, 0, 1, v);
 #pragma unroll
     for (int j = 0; j < 32; ++j) gv[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, goff, j * 32 * 4096, 0));
     fwht_regs_t<32>(v);
@@ -677,12 +729,12 @@ __global__ __launch_bounds__(1024) void k_afjl_tail_1024w(const LayerDesc *__res
   }
 }
 
-void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin, const float *part, int64_t bc,
-                      int64_t b_begin, int64_t batch, float *out, bool accumulate, hipStream_t st) {
+void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin, int split, const float *part,
+                      int64_t bc, int64_t b_begin, int64_t batch, float *out, bool accumulate, hipStream_t st) {
   // the register tails read each layer's partials through a buffer resource
   bool small_parts = true;
   for (int l = l_begin; l < l_end; ++l)
-    small_parts = small_parts && (int64_t)s->layers[l].n_items * bc * s->Lw * 4 < (1ll << 31);
+    small_parts = small_parts && (int64_t)s->layers[l].n_items * split * bc * s->Lw * 4 < (1ll << 31);
   if (s->R == 1024 && s->Lw == 1024 && small_parts) {
     const int64_t rows = (batch - b_begin) < bc ? (batch - b_begin) : bc;
     hipLaunchKernelGGL(k_afjl_tail_1024w, dim3(32u, (unsigned)rows), dim3(1024), 0, st, s->d_layers, s->d_rslot,
@@ -707,19 +759,22 @@ void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin
     }
     grp.bound[++ng] = l_end;
     float *ysum = s->ws + (s->ws_bytes / 4 - (int64_t)kTailGroups * bc * s->D);
+    // split items of a call with few layers: the shares over what is left of the 16 sums, each through H_R
+    // and G by itself (a head of 4 layers in 16 shares: this kernel 9.6 -> 4.9 us)
+    const int zg = split > 1 ? std::max(1, std::min(kTailGroups / ng, split)) : 1;
     const int64_t threads = bc * Lw * (R > 32 ? 2 : 1);
-    dim3 grid((unsigned)((threads + 255) / 256), (unsigned)ng);
+    dim3 grid((unsigned)((threads + 255) / 256), (unsigned)(ng * zg));
 #define SK_TAIL(RR)                                                                                              \
   case RR:                                                                                                       \
     hipLaunchKernelGGL(k_afjl_tail_reg<RR>, grid, dim3(256), 0, st, s->d_layers, s->d_rslot, s->d_rfirst, part,  \
-                       s->d_gtab, grp, item_begin, Lw, s->D, bc, b_begin, batch, ysum);                          \
+                       s->d_gtab, grp, item_begin, split, zg, Lw, s->D, bc, b_begin, batch, ysum);                         \
     break;
     switch (R) {
       SK_TAIL(1) SK_TAIL(2) SK_TAIL(4) SK_TAIL(8) SK_TAIL(16) SK_TAIL(32) SK_TAIL(64)
       default: break;
     }
 #undef SK_TAIL
-    launch_reduce_partials(ysum, ng, bc, s->D, b_begin, out, accumulate, st);
+    launch_reduce_partials(ysum, ng * zg, bc, s->D, b_begin, out, accumulate, st);
     SK_CHECK_LAUNCH();
     return;
   }

@@ -78,10 +78,13 @@ void run_afjlf_T(sk_sketch *s, int l0, int l1, const float *z, int64_t b_begin, 
                  int64_t ws_floats, void *const *outs, int out_dtype, const void *const *theta0, hipStream_t st);
 
 // ---- AFJL ----
-void launch_afjl_fold(const sk_sketch *s, const PtrPack &ptrs, int first_layer, int dtype, bool vec, int64_t batch,
-                      int64_t b_begin, int64_t bc, int item_begin, int item_end, float *part, hipStream_t st);
-void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin, const float *part, int64_t bc,
-                      int64_t b_begin, int64_t batch, float *out, bool accumulate, hipStream_t st);
+// split: workgroups (and partial sums) per fold item, from afjl_fold_split for the whole call.
+int afjl_fold_split(const sk_sketch *s, int l0, int l1, int64_t bc, int64_t rows);
+void launch_afjl_fold(const sk_sketch *s, const PtrPack &ptrs, int first_layer, int dtype, int64_t batch,
+                      int64_t b_begin, int64_t bc, int item_begin, int item_end, int split, float *part,
+                      hipStream_t st);
+void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin, int split, const float *part,
+                      int64_t bc, int64_t b_begin, int64_t batch, float *out, bool accumulate, hipStream_t st);
 // AFJL transpose over a group of up to kMaxPtrs consecutive layers: g_l . z
 // for all of them into w ([layer][vector][D]), then (after the transform of
 // all ng * bc vectors) every output row of the group in one launch.

@@ -1,0 +1,35 @@
+"""AFJL calls whose fold items are split over several workgroups (small calls), and rows that start at any
+element (odd sizes in fp32 and bf16): against the fp64 oracle, one to 33 vectors, accumulated and in chunks of a
+small workspace."""
+import pytest
+import torch
+
+import oracle as O
+from test_gpu_parity import TOL_F32, dev, oracle_in, rand_inputs, rel_err  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# D = 256 (Lw < 1024), 1024 (one destination row), 4096 (R = 4) and 65536 (R = 64, two threads per column);
+# items of one row, of a full 256 and a 257th, and layers that pad to N' = D
+LAYERS = [(1, 2), (1, 769), (33, 1024), (257, 1024), (3, 100001)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,batch,ws_mb", [(256, 1, None), (256, 3, None), (1024, 1, None), (1024, 9, None),
+                                           (4096, 1, None), (4096, 2, None), (4096, 33, None), (8192, 8, 16),
+                                           (65536, 1, None), (65536, 5, 16)])
+def test_afjl_split_items(D, batch, ws_mb, dtype, dev, monkeypatch):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    if ws_mb is not None:
+        monkeypatch.setenv("SK_WORKSPACE_MB", str(ws_mb))
+    seed = 17
+    xs = rand_inputs(LAYERS, batch, seed, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ref = O.apply("afjl", LAYERS, D, seed, [oracle_in(x)[0] for x in xs], dtype=dtype)
+    s = Sketch("afjl", LAYERS, D, seed, device=dev)
+    xd = [x.to(dev) for x in xs]
+    y = s.apply(xd)
+    assert rel_err(y.cpu().numpy(), ref) < TOL_F32
+    y2 = s.apply(xd[:2])
+    s.apply(xd[2:], out=y2, first_layer=2, accumulate=True)
+    assert rel_err(y2.cpu().numpy(), ref) < TOL_F32
+    s.close()
