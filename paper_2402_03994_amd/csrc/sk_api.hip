@@ -110,7 +110,7 @@ int64_t per_vector_bytes(const sk_sketch *s, int l0, int l1, bool transpose) {
         if (transpose) b = s->D * 4;
         break;
       case SK_AFFD:
-        b = transpose ? ld.np * 4 : (ld.np + (1ll << ld.lo_len_lg) + s->D) * 4;
+        b = transpose ? (ld.np + s->D) * 4 : (ld.np + (1ll << ld.lo_len_lg) + s->D) * 4;
         break;
       case SK_FJL:
         b = ld.np * 4;
@@ -1110,6 +1110,15 @@ int sketch_apply_T(sk_sketch *s, const float *z, int64_t batch, void *const *out
       continue;
     }
     for (int l = l0; l < l1; ++l) {
+      if (s->kind == SK_AFFD && affd_T_grouped(s, l)) {
+        const AffdTTGroup g = affd_T_group(s, l, l1, bc, out + (l - l0), theta0 ? theta0 + (l - l0) : nullptr);
+        int64_t bytes = 0;
+        for (int i = 0; i < g.n; ++i) bytes += bc * s->layers[l + i].n * osz + (g.th[i] ? s->layers[l + i].n * 4 : 0);
+        SK_PROF(SK_PROF_PROLOG, bc * s->D * 4, run_affd_T(s, g, z, b0, bc, out_dtype, 1, st));
+        SK_PROF(SK_PROF_GATHER, bytes, run_affd_T(s, g, z, b0, bc, out_dtype, 2, st));
+        l += g.n - 1;
+        continue;
+      }
       const LayerDesc &ld = s->layers[l];
       void *o = out[l - l0];
       const float *th = theta0 ? (const float *)theta0[l - l0] : nullptr;

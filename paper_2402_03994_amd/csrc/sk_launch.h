@@ -175,6 +175,25 @@ void launch_mul_gauss(const sk_sketch *s, int layer, float *w, int64_t bc, hipSt
 void launch_affd_T_out(const sk_sketch *s, int layer, const float *w, int64_t b_begin, int64_t bc, void *out,
                        int out_dtype, const float *theta0, hipStream_t st);
 
+// AFFD transposes of a group of layers (sk_affd_tt.hip): U (bc x D) and W (bc x live slabs) per layer at float
+// offsets into the workspace.
+struct AffdTTGroup {
+  int32_t n, spw;
+  int32_t layer[kMaxPtrs];
+  uint32_t blk0[kMaxPtrs];
+  float scale[kMaxPtrs];
+  int64_t u_off[kMaxPtrs], w_off[kMaxPtrs];
+  const float *m[kMaxPtrs];
+  void *out[kMaxPtrs];
+  const float *th[kMaxPtrs];
+};
+bool affd_T_grouped(const sk_sketch *s, int layer);
+// The run of such layers from l0 on that fits the workspace (at least one); out, theta0: from layer l0 on.
+AffdTTGroup affd_T_group(const sk_sketch *s, int l0, int l1, int64_t bc, void *const *out, const void *const *theta0);
+// phases: bit 0 = z to W, bit 1 = the outputs
+void run_affd_T(const sk_sketch *s, const AffdTTGroup &g, const float *z, int64_t b_begin, int64_t bc, int out_dtype,
+                int phases, hipStream_t st);
+
 // ---- FJL ----
 void launch_fjl_gather(const sk_sketch *s, int layer, const float *w, int64_t b_begin, int64_t bc, float *out,
                        bool accumulate, hipStream_t st);

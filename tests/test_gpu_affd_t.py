@@ -1,0 +1,42 @@
+"""AFFD transposes of layer groups (rows of z, columns, output rows): every tile width of the one-slab layers
+(second digit of 2 to 512 values), one- and several-slab layers with the stored M tables, layers in between that
+take the pass-based chain (no tables), more layers than one launch takes, odd sizes and bf16 outputs at odd
+starts, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from test_gpu_parity import TOL_BF16, TOL_F32, dev, rel_err  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# (D, shapes, flags, SK_WORKSPACE_MB)
+CASES = [(2048, [(1, 3), (3, 1000), (1, 4099), (5, 3001), (33, 1023), (1, 100003)], 0, None),
+         (16384, [(1, 768), (1, 16384), (3, 10001), (1, 2 ** 17 + 3), (1, 2 ** 19 - 5), (1, 2 ** 18 + 1)], 0, None),
+         (4096, [(1, 2 ** 20 - 3), (1, 77), (1, 2 ** 20 + 5), (3, 2 ** 20 + 11), (1, 9 * 2 ** 20 + 5)], 0, None),
+         (1 << 17, [(1, 2 ** 20 + 5), (1, 70001), (1, 2 ** 20)], 1, None),
+         (1 << 20, [(1, 9), (1, 2 ** 21 + 7)], 0, None),
+         (2048, [(1, 100 + 37 * i) for i in range(70)] + [(1, 2 ** 20 + 1)], 0, None),
+         (65536, [(1, 2 ** 20 + 5), (1, 768), (1, 2 ** 21 + 9), (2, 2305)], 0, 22)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case,batch", [(i, b) for i in range(len(CASES)) for b in ((1, 3) if i != 4 else (1,))])
+def test_affd_transpose_groups(case, batch, dtype, dev, monkeypatch):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    D, shapes, flags, ws_mb = CASES[case]
+    if ws_mb is not None:  # one layer of three vectors in several chunks and groups
+        monkeypatch.setenv("SK_WORKSPACE_MB", str(ws_mb))
+    seed = 900 + case
+    s = Sketch("affd", shapes, D, seed, device=dev, flags=flags)
+    g = torch.Generator().manual_seed(seed)
+    z = torch.randn((batch, D), generator=g)
+    th = [torch.randn(r * c, generator=g) * 0.02 if i % 2 else None for i, (r, c) in enumerate(shapes)]
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    outs = s.apply_T(z.to(dev), out_dtype=tdt, theta0=[None if t is None else t.to(dev) for t in th])
+    refs = O.apply_T("affd", shapes, D, seed, z.numpy().astype(np.float64),
+                     theta0=[None if t is None else t.numpy() for t in th])
+    for o, r in zip(outs, refs):
+        assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL_F32)
+    s.close()
