@@ -639,12 +639,18 @@ void launch_affd_mtab(const sk_sketch *s, int layer, float *m, hipStream_t st) {
 // for each listed layer in order, H_l along the 16 rows of its G, gather
 // pi2_l(b) and add (times the layer's scale) into registers; out is written
 // once.  The next layer's G rows are loaded during the current transform.
+// With few vectors the layers are shared out over blockIdx.z (each share's sum
+// to part[z][v][D], added in order afterwards): 50 layers one after the other
+// on 32 workgroups (8 vectors, D = 2^16) took 440 us.
 __global__ __launch_bounds__(256) void k_affdT_outm(const LayerDesc *__restrict__ layers,
                                                     const uint16_t *__restrict__ ptab, OutLayers ol, int R,
                                                     int64_t D, int64_t b_begin, int64_t gstride,
-                                                    float *__restrict__ out, int accumulate) {
+                                                    float *__restrict__ out, int accumulate,
+                                                    float *__restrict__ part) {
   using L = Lds1024<16>;
   __shared__ __align__(16) float s[L::kFloats];
+  const int per = (ol.n + gridDim.z - 1) / gridDim.z;
+  const int j0 = blockIdx.z * per, j1 = min(j0 + per, ol.n);  // never empty (see the launcher)
   const int a0 = blockIdx.x * 16;
   const int na = (R - a0) < 16 ? (R - a0) : 16;
   const int64_t v = blockIdx.y;
@@ -672,8 +678,8 @@ __global__ __launch_bounds__(256) void k_affdT_outm(const LayerDesc *__restrict_
         }
       }
   };
-  fetch(0);
-  for (int j = 0; j < ol.n; ++j) {
+  fetch(j0);
+  for (int j = j0; j < j1; ++j) {
     __syncthreads();  // the previous layer's gathers from s are done
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -686,7 +692,7 @@ __global__ __launch_bounds__(256) void k_affdT_outm(const LayerDesc *__restrict_
         s[L::idx(4 * q + 3, l)] = g[k][q].w;
       }
     }
-    if (j + 1 < ol.n) fetch(j + 1);
+    if (j + 1 < j1) fetch(j + 1);
     __syncthreads();
     fwht1024_lds<16>(s);
     const LayerDesc &ld = layers[ol.layer[j]];
@@ -701,11 +707,12 @@ __global__ __launch_bounds__(256) void k_affdT_outm(const LayerDesc *__restrict_
       for (int k = 0; k < 4; ++k) acc[i][k] += s[L::idx(i, src[k])] * sc;
   }
   for (int i = 0; i < na; ++i) {
-    float *o = out + (b_begin + v) * D + (int64_t)(a0 + i) * 1024;
+    float *o = (part ? part + ((int64_t)blockIdx.z * gridDim.y + v) * D : out + (b_begin + v) * D) +
+               (int64_t)(a0 + i) * 1024;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int b = threadIdx.x + 256 * k;
-      o[b] = accumulate ? o[b] + acc[i][k] : acc[i][k];
+      o[b] = accumulate && !part ? o[b] + acc[i][k] : acc[i][k];
     }
   }
 }
@@ -844,10 +851,18 @@ void run_affd_transposed(const sk_sketch *s, int layer, const void *x, int dtype
 }
 
 void run_affd_transposed_outm(const sk_sketch *s, const OutLayers &ol, int64_t gstride, int64_t b_begin,
-                              int64_t gb, float *out, bool accumulate, hipStream_t st) {
+                              int64_t gb, float *out, bool accumulate, float *part, int64_t max_groups,
+                              hipStream_t st) {
   const int R = (int)(s->D / 1024);
-  hipLaunchKernelGGL(k_affdT_outm, dim3((unsigned)((R + 15) / 16), (unsigned)gb), dim3(256), 0, st, s->d_layers,
-                     s->d_ptab, ol, R, s->D, b_begin, gstride, out, (int)accumulate);
+  const unsigned gx = (unsigned)((R + 15) / 16);
+  // shares of the layers: 512 workgroups (two per CU, by the 66 KB of LDS), at least two layers each, 16 sums at most
+  int64_t nz = std::min<int64_t>({ol.n / 2, 512 / std::max<int64_t>(1, gx * gb), part ? max_groups : 0, 16});
+  if (nz < 2) nz = 1;
+  const int64_t per = (ol.n + nz - 1) / nz;
+  nz = (ol.n + per - 1) / per;
+  hipLaunchKernelGGL(k_affdT_outm, dim3(gx, (unsigned)gb, (unsigned)nz), dim3(256), 0, st, s->d_layers, s->d_ptab, ol,
+                     R, s->D, b_begin, gstride, out, (int)accumulate, nz > 1 ? part : nullptr);
+  if (nz > 1) launch_reduce_partials(part, nz, gb, s->D, b_begin, out, accumulate, st);
   (void)hipGetLastError();
 }
 

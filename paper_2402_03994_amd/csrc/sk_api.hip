@@ -789,7 +789,9 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
         OutLayers ol{};
         auto flush = [&]() {
           if (!ol.n) return;
-          SK_PROF(SK_PROF_GATHER, bc * s->D * 4, run_affd_transposed_outm(s, ol, s->D, b0, bc, out, acc_now, st));
+          // the W^T region is free until the next layer
+          SK_PROF(SK_PROF_GATHER, bc * s->D * 4,
+                  run_affd_transposed_outm(s, ol, s->D, b0, bc, out, acc_now, s->ws, wt_region / gslot, st));
           acc_now = true;
           ol.n = 0;
         };
@@ -813,8 +815,42 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
             }
           }
         };
+        // layers that go through the grouped passes in a call of this size (those that do not fit the workspace
+        // stay with the paths below)
+        std::vector<char> done(l1 - l0, 0);
+        std::vector<int> fl;
+        for (int l = l0; l < l1; ++l)
+          if (affd_F_grouped(s, l, bc)) fl.push_back(l);
+        for (size_t i = 0; i < fl.size();) {
+          int nl = 0;
+          const AffdTTGroup g = affd_F_group(s, fl.data() + i, (int)(fl.size() - i), l0, bc, grads, &nl);
+          if (!nl) {
+            ++i;
+            continue;
+          }
+          int64_t in = 0;
+          for (int k = 0; k < nl; ++k) {
+            in += bc * s->layers[fl[i + k]].n * esz;
+            done[fl[i + k] - l0] = 1;
+          }
+          SK_PROF(SK_PROF_AFFD_ROWS, in, run_affd_F(s, g, dtype, b0, bc, 1, st));
+          SK_PROF(SK_PROF_AFFD_FOLD, 0, run_affd_F(s, g, dtype, b0, bc, 2, st));
+          OutLayers o{};
+          o.n = g.n;
+          for (int k = 0; k < g.n; ++k) {
+            o.layer[k] = g.layer[k];
+            o.scale[k] = g.scale[k];
+            o.g[k] = s->ws + g.u_off[k];
+          }
+          // every layer's W (free by now) is at least bc x D
+          SK_PROF(SK_PROF_GATHER, bc * s->D * 4,
+                  run_affd_transposed_outm(s, o, s->D, b0, bc, out, acc_now, s->ws + bc * s->D * g.n, nl, st));
+          acc_now = true;
+          i += nl;
+        }
         for (int l = l0; l < l1; ++l) {
           const LayerDesc &ld = s->layers[l];
+          if (done[l - l0]) continue;
           if (affd_small_path(s, l)) {
             small.push_back(l);
             continue;
@@ -842,7 +878,8 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
               one.layer[0] = l;
               one.scale[0] = affd_transposed_out_scale(s, l);
               one.g[0] = gbuf;
-              SK_PROF(SK_PROF_GATHER, gb * s->D * 4, run_affd_transposed_outm(s, one, s->D, g0, gb, out, acc_now, st));
+              SK_PROF(SK_PROF_GATHER, gb * s->D * 4,
+                      run_affd_transposed_outm(s, one, s->D, g0, gb, out, acc_now, nullptr, 0, st));
             }
             acc_now = true;
             continue;

@@ -161,8 +161,10 @@ struct OutLayers {
   float scale[kMaxPtrs];
   const float *g[kMaxPtrs];
 };
+// part: room for max_groups sums of [gb, D] (workgroups share the layers out while the grid is small), or null.
 void run_affd_transposed_outm(const sk_sketch *s, const OutLayers &ol, int64_t gstride, int64_t b_begin,
-                              int64_t gb, float *out, bool accumulate, hipStream_t st);
+                              int64_t gb, float *out, bool accumulate, float *part, int64_t max_groups,
+                              hipStream_t st);
 float affd_transposed_out_scale(const sk_sketch *s, int layer);
 void launch_affd_prolog(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc,
                         float *w, hipStream_t st);
@@ -180,6 +182,7 @@ void launch_affd_T_out(const sk_sketch *s, int layer, const float *w, int64_t b_
 struct AffdTTGroup {
   int32_t n, spw;
   int32_t layer[kMaxPtrs];
+  int32_t t0[kMaxPtrs];  // forward: first slab of the entry's run
   uint32_t blk0[kMaxPtrs];
   float scale[kMaxPtrs];
   int64_t u_off[kMaxPtrs], w_off[kMaxPtrs];
@@ -193,6 +196,15 @@ AffdTTGroup affd_T_group(const sk_sketch *s, int l0, int l1, int64_t bc, void *c
 // phases: bit 0 = z to W, bit 1 = the outputs
 void run_affd_T(const sk_sketch *s, const AffdTTGroup &g, const float *z, int64_t b_begin, int64_t bc, int out_dtype,
                 int phases, hipStream_t st);
+// Does the layer take the passes of sk_affd_tt.hip forward, in a call of bc vectors?
+bool affd_F_grouped(const sk_sketch *s, int layer, int64_t bc);
+// The forward by those passes: entries (layer, run of slabs) of the first *taken listed layers (inputs x from layer
+// l0 on, held in `out`), as many as fit the workspace.  Phases: bit 0 = rows, bit 1 = columns; G^T of entry i is at
+// u_off[i], for run_affd_transposed_outm.
+AffdTTGroup affd_F_group(const sk_sketch *s, const int *layers, int count, int l0, int64_t bc, const void *const *x,
+                         int *taken);
+void run_affd_F(const sk_sketch *s, const AffdTTGroup &g, int dtype, int64_t b_begin, int64_t bc, int phases,
+                hipStream_t st);
 
 // ---- FJL ----
 void launch_fjl_gather(const sk_sketch *s, int layer, const float *w, int64_t b_begin, int64_t bc, float *out,

@@ -1,4 +1,5 @@
-"""AFFD transposes of layer groups (rows of z, columns, output rows): every tile width of the one-slab layers
+"""AFFD transposes of layer groups (rows of z, columns, output rows), and forwards of few vectors by the same passes
+(and of three vectors, whose output pass shares the layers out): every tile width of the one-slab layers
 (second digit of 2 to 512 values), one- and several-slab layers with the stored M tables, layers in between that
 take the pass-based chain (no tables), more layers than one launch takes, odd sizes and bf16 outputs at odd
 starts, against the fp64 oracle."""
@@ -7,7 +8,7 @@ import pytest
 import torch
 
 import oracle as O
-from test_gpu_parity import TOL_BF16, TOL_F32, dev, rel_err  # noqa: F401
+from test_gpu_parity import TOL_BF16, TOL_F32, dev, oracle_in, rand_inputs, rel_err  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -39,4 +40,23 @@ def test_affd_transpose_groups(case, batch, dtype, dev, monkeypatch):  # noqa: F
                      theta0=[None if t is None else t.numpy() for t in th])
     for o, r in zip(outs, refs):
         assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL_F32)
+    s.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case,batch", [(i, b) for i in range(len(CASES)) for b in ((1, 2, 3) if i != 4 else (1,))])
+def test_affd_few_vectors(case, batch, dtype, dev, monkeypatch):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    D, shapes, flags, ws_mb = CASES[case]
+    if ws_mb is not None:
+        monkeypatch.setenv("SK_WORKSPACE_MB", str(ws_mb))
+    seed = 950 + case
+    s = Sketch("affd", shapes, D, seed, device=dev, flags=flags)
+    xs = rand_inputs(shapes, batch, seed, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ref = O.apply("affd", shapes, D, seed, [oracle_in(x)[0] for x in xs], dtype=dtype)
+    xd = [x.to(dev) for x in xs]
+    y = s.apply(xd)
+    assert rel_err(y.cpu().numpy(), ref) < TOL_F32
+    s.apply(xd, out=y, accumulate=True)
+    assert rel_err(y.cpu().numpy(), 2 * ref) < TOL_F32
     s.close()
