@@ -977,15 +977,10 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
             SK_PROF(SK_PROF_FFD, 0,
                     run_ffd_large_fwd(s, l, grads[l - l0], dtype, b0, bc, out, accumulate || l > l0, 2, st));
           } else {
-            const int64_t nlive = ffd_live_blocks(s, l);
-            float *w = s->ws, *w2 = s->ws + bc * nlive * s->D;
             SK_PROF(SK_PROF_PROLOG, bc * s->layers[l].n * esz,
-                    launch_ffd_copy_blocks(s, l, grads[l - l0], dtype, b0, bc, w, st));
-            SK_PROF(SK_PROF_FWHT, 0, fwht_inplace(w, bc * nlive, lgD, st));
-            SK_PROF(SK_PROF_FFD, 0, launch_ffd_gperm_fwd(s, l, w, bc, w2, st));
-            SK_PROF(SK_PROF_FWHT, 0, fwht_inplace(w2, bc * nlive, lgD, st));
-            SK_PROF(SK_PROF_GATHER, (l == l1 - 1 ? bc * s->D * 4 : 0),
-                    launch_ffd_sum_signed(s, l, w2, b0, bc, out, accumulate || l > l0, st));
+                    run_ffd_mid_fwd(s, l, grads[l - l0], dtype, b0, bc, out, accumulate || l > l0, 1, st));
+            SK_PROF(SK_PROF_FFD, 0,
+                    run_ffd_mid_fwd(s, l, grads[l - l0], dtype, b0, bc, out, accumulate || l > l0, 2, st));
           }
         }
         break;
@@ -1202,13 +1197,8 @@ int sketch_apply_T(sk_sketch *s, const float *z, int64_t batch, void *const *out
             SK_PROF(SK_PROF_FFD, 0, run_ffd_large_T(s, l, z, b0, bc, o, out_dtype, th, 1, st));
             SK_PROF(SK_PROF_GATHER, obytes + bc * s->D * 4, run_ffd_large_T(s, l, z, b0, bc, o, out_dtype, th, 2, st));
           } else {
-            const int64_t nlive = ffd_live_blocks(s, l);
-            float *w = s->ws, *w2 = s->ws + bc * nlive * s->D;
-            SK_PROF(SK_PROF_PROLOG, bc * s->D * 4, launch_ffd_expand_z(s, l, z, b0, bc, w, st));
-            SK_PROF(SK_PROF_FWHT, 0, fwht_inplace(w, bc * nlive, lgD, st));
-            SK_PROF(SK_PROF_FFD, 0, launch_ffd_permg_T(s, l, w, bc, w2, st));
-            SK_PROF(SK_PROF_FWHT, 0, fwht_inplace(w2, bc * nlive, lgD, st));
-            SK_PROF(SK_PROF_GATHER, obytes, launch_ffd_T_out(s, l, w2, b0, bc, o, out_dtype, th, st));
+            SK_PROF(SK_PROF_FFD, 0, run_ffd_mid_T(s, l, z, b0, bc, o, out_dtype, th, 1, st));
+            SK_PROF(SK_PROF_GATHER, obytes + bc * s->D * 4, run_ffd_mid_T(s, l, z, b0, bc, o, out_dtype, th, 2, st));
           }
           break;
         case SK_QKH:

@@ -2073,171 +2073,6 @@ void launch_ffd_small_T(const sk_sketch *s, int layer, const float *z, int64_t b
   SK_CHECK_LAUNCH();
 }
 
-// --- large D: workspace w[v][bb][i], bb < nlive ---
-template <bool BF16>
-__global__ void k_ffd_copy_blocks(const LayerDesc *__restrict__ layers, int layer, const void *__restrict__ x,
-                                  int64_t span, int64_t b_begin, float *__restrict__ w) {
-  const LayerDesc &ld = layers[layer];
-  const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;  // within the live span
-  if (j >= span) return;
-  const int64_t v = blockIdx.y;
-  float val = 0.0f;
-  if (j < ld.n) {
-    const int64_t e = (b_begin + v) * ld.n + j;
-    val = BF16 ? bf16_to_f32(((const uint16_t *)x)[e]) : ((const float *)x)[e];
-  }
-  w[v * span + j] = val;
-}
-
-void launch_ffd_copy_blocks(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc,
-                            float *w, hipStream_t st) {
-  const int64_t span = ffd_live_blocks(s, layer) * s->D;
-  dim3 grid((unsigned)((span + 255) / 256), (unsigned)bc);
-  if (dtype == SK_BF16)
-    hipLaunchKernelGGL(k_ffd_copy_blocks<true>, grid, dim3(256), 0, st, s->d_layers, layer, x, span, b_begin, w);
-  else
-    hipLaunchKernelGGL(k_ffd_copy_blocks<false>, grid, dim3(256), 0, st, s->d_layers, layer, x, span, b_begin, w);
-  SK_CHECK_LAUNCH();
-}
-
-// w2[v][bb][pi_b(k)] = g_{b,k} w[v][bb][k]; one thread per 4 consecutive k, all vectors.
-__global__ void k_ffd_gperm_fwd(const LayerDesc *__restrict__ layers, int layer, const float *__restrict__ w,
-                                int lgD, int64_t nlive, int64_t bc, float *__restrict__ w2, Key key) {
-  const LayerDesc &ld = layers[layer];
-  const int64_t D = 1ll << lgD;
-  const int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * 4;
-  const int64_t bb = t >> lgD;
-  if (bb >= nlive) return;
-  const int64_t k0 = t & (D - 1);
-  const PermKey pk = perm_key((uint32_t)ld.layer_id, ST_FFDPERM, (uint32_t)bb, (uint32_t)lgD, key);
-  float g[4];
-  gauss4((uint64_t)(bb * D + k0) >> 2, (uint32_t)ld.layer_id, ST_GAUSS, key, g);
-  uint32_t p[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) p[q] = perm_fwd(pk, (uint32_t)(k0 + q));
-  const int64_t span = nlive * D;
-  for (int64_t v = 0; v < bc; ++v) {
-    const float4 x = *(const float4 *)(w + v * span + t);
-    float *dst = w2 + v * span + bb * D;
-    dst[p[0]] = g[0] * x.x;
-    dst[p[1]] = g[1] * x.y;
-    dst[p[2]] = g[2] * x.z;
-    dst[p[3]] = g[3] * x.w;
-  }
-}
-
-void launch_ffd_gperm_fwd(const sk_sketch *s, int layer, const float *w, int64_t bc, float *w2, hipStream_t st) {
-  const int lgD = log2_exact(s->D);
-  if (lgD < 4 || lgD > 20) return;  // create() admits 2^4 <= D <= 2^20 only
-  const int64_t nlive = ffd_live_blocks(s, layer);
-  const int64_t th = nlive * s->D / 4;
-  hipLaunchKernelGGL(k_ffd_gperm_fwd, dim3((unsigned)((th + 255) / 256)), dim3(256), 0, st, s->d_layers, layer, w,
-                     lgD, nlive, bc, w2, s->key);
-  SK_CHECK_LAUNCH();
-}
-
-__global__ void k_ffd_sum_signed(const LayerDesc *__restrict__ layers, int layer, const float *__restrict__ w2,
-                                 int64_t D, int64_t nlive, int64_t b_begin, int64_t bc, float *__restrict__ out,
-                                 int accumulate, Key key) {
-  const LayerDesc &ld = layers[layer];
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= D) return;
-  const int64_t v = blockIdx.y;
-  float acc = 0.0f;
-  for (int64_t bb = 0; bb < nlive; ++bb) {
-    const int64_t j = bb * D + i;
-    const uint32_t bit = (sign_word((uint64_t)j, (uint32_t)ld.layer_id, key) >> (j & 31)) & 1u;
-    acc += flip(w2[v * nlive * D + j], bit);
-  }
-  float *o = out + (b_begin + v) * D + i;
-  *o = accumulate ? *o + acc : acc;
-}
-
-void launch_ffd_sum_signed(const sk_sketch *s, int layer, const float *w2, int64_t b_begin, int64_t bc, float *out,
-                           bool accumulate, hipStream_t st) {
-  dim3 grid((unsigned)((s->D + 255) / 256), (unsigned)bc);
-  hipLaunchKernelGGL(k_ffd_sum_signed, grid, dim3(256), 0, st, s->d_layers, layer, w2, s->D,
-                     ffd_live_blocks(s, layer), b_begin, bc, out, (int)accumulate, s->key);
-  SK_CHECK_LAUNCH();
-}
-
-__global__ void k_ffd_expand_z(const LayerDesc *__restrict__ layers, int layer, const float *__restrict__ z,
-                               int lgD, int64_t nlive, int64_t b_begin, float *__restrict__ w, Key key) {
-  const LayerDesc &ld = layers[layer];
-  const int64_t D = 1ll << lgD;
-  const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= nlive * D) return;
-  const int64_t v = blockIdx.y;
-  const uint32_t bit = (sign_word((uint64_t)j, (uint32_t)ld.layer_id, key) >> (j & 31)) & 1u;
-  w[v * nlive * D + j] = flip(z[(b_begin + v) * D + (j & (D - 1))], bit);
-}
-
-void launch_ffd_expand_z(const sk_sketch *s, int layer, const float *z, int64_t b_begin, int64_t bc, float *w,
-                         hipStream_t st) {
-  const int lgD = log2_exact(s->D);
-  if (lgD < 4 || lgD > 20) return;  // create() admits 2^4 <= D <= 2^20 only
-  const int64_t nlive = ffd_live_blocks(s, layer);
-  dim3 grid((unsigned)((nlive * s->D + 255) / 256), (unsigned)bc);
-  hipLaunchKernelGGL(k_ffd_expand_z, grid, dim3(256), 0, st, s->d_layers, layer, z, lgD, nlive, b_begin, w, s->key);
-  SK_CHECK_LAUNCH();
-}
-
-// w2[v][bb][i] = g_{b,i} w[v][bb][pi_b(i)]
-__global__ void k_ffd_permg_T(const LayerDesc *__restrict__ layers, int layer, const float *__restrict__ w, int lgD,
-                              int64_t nlive, int64_t bc, float *__restrict__ w2, Key key) {
-  const LayerDesc &ld = layers[layer];
-  const int64_t D = 1ll << lgD;
-  const int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * 4;
-  const int64_t bb = t >> lgD;
-  if (bb >= nlive) return;
-  const int64_t i0 = t & (D - 1);
-  const PermKey pk = perm_key((uint32_t)ld.layer_id, ST_FFDPERM, (uint32_t)bb, (uint32_t)lgD, key);
-  float g[4];
-  gauss4((uint64_t)(bb * D + i0) >> 2, (uint32_t)ld.layer_id, ST_GAUSS, key, g);
-  uint32_t p[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) p[q] = perm_fwd(pk, (uint32_t)(i0 + q));
-  const int64_t span = nlive * D;
-  for (int64_t v = 0; v < bc; ++v) {
-    const float *src = w + v * span + bb * D;
-    float4 o = make_float4(g[0] * src[p[0]], g[1] * src[p[1]], g[2] * src[p[2]], g[3] * src[p[3]]);
-    *(float4 *)(w2 + v * span + t) = o;
-  }
-}
-
-void launch_ffd_permg_T(const sk_sketch *s, int layer, const float *w, int64_t bc, float *w2, hipStream_t st) {
-  const int lgD = log2_exact(s->D);
-  if (lgD < 4 || lgD > 20) return;  // create() admits 2^4 <= D <= 2^20 only
-  const int64_t nlive = ffd_live_blocks(s, layer);
-  const int64_t th = nlive * s->D / 4;
-  hipLaunchKernelGGL(k_ffd_permg_T, dim3((unsigned)((th + 255) / 256)), dim3(256), 0, st, s->d_layers, layer, w, lgD,
-                     nlive, bc, w2, s->key);
-  SK_CHECK_LAUNCH();
-}
-
-__global__ void k_ffd_T_out(const LayerDesc *__restrict__ layers, int layer, const float *__restrict__ w2,
-                            int64_t span, int64_t b_begin, void *__restrict__ out, int out_dtype,
-                            const float *__restrict__ theta0) {
-  const LayerDesc &ld = layers[layer];
-  const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= ld.n) return;
-  const int64_t v = blockIdx.y;
-  store_out(out, out_dtype, (b_begin + v) * ld.n + j, w2[v * span + j] + (theta0 ? theta0[j] : 0.0f));
-}
-
-void launch_ffd_T_out(const sk_sketch *s, int layer, const float *w2, int64_t b_begin, int64_t bc, void *out,
-                      int out_dtype, const float *theta0, hipStream_t st) {
-  const LayerDesc &ld = s->layers[layer];
-  const int64_t span = ffd_live_blocks(s, layer) * s->D;
-  dim3 grid((unsigned)((ld.n + 255) / 256), (unsigned)bc);
-  hipLaunchKernelGGL(k_ffd_T_out, grid, dim3(256), 0, st, s->d_layers, layer, w2, span, b_begin, out, out_dtype,
-                     theta0);
-  SK_CHECK_LAUNCH();
-}
-
-// ===========================================================================
-// Tables and stream export.
-// ===========================================================================
 __global__ void k_gauss_table(const LayerDesc *__restrict__ layers, int nl, int64_t D, float *__restrict__ gtab,
                               Key key) {
   const int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * 4;

@@ -237,16 +237,13 @@ void launch_reduce_partials(const float *part, int64_t nslots, int64_t bc, int64
                             bool accumulate, hipStream_t st);
 void launch_ffd_small_T(const sk_sketch *s, int layer, const float *z, int64_t b_begin, int64_t bc, void *out,
                         int out_dtype, const float *theta0, const float *tab, hipStream_t st);
-void launch_ffd_copy_blocks(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc,
-                            float *w, hipStream_t st);
-void launch_ffd_gperm_fwd(const sk_sketch *s, int layer, const float *w, int64_t bc, float *w2, hipStream_t st);
-void launch_ffd_sum_signed(const sk_sketch *s, int layer, const float *w2, int64_t b_begin, int64_t bc, float *out,
-                           bool accumulate, hipStream_t st);
-void launch_ffd_expand_z(const sk_sketch *s, int layer, const float *z, int64_t b_begin, int64_t bc, float *w,
-                         hipStream_t st);
-void launch_ffd_permg_T(const sk_sketch *s, int layer, const float *w, int64_t bc, float *w2, hipStream_t st);
-void launch_ffd_T_out(const sk_sketch *s, int layer, const float *w2, int64_t b_begin, int64_t bc, void *out,
-                      int out_dtype, const float *theta0, hipStream_t st);
+// 2^14 <= D <= 2^19 (sk_ffd_m.hip); phases: bit 0 = forward: the pass that reads x, transpose: all but the output
+// pass; bit 1 = the rest
+bool ffd_mid_path(const sk_sketch *s);
+void run_ffd_mid_fwd(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc, float *out,
+                     bool accumulate, int phases, hipStream_t st);
+void run_ffd_mid_T(const sk_sketch *s, int layer, const float *z, int64_t b_begin, int64_t bc, void *out, int out_dtype,
+                   const float *theta0, int phases, hipStream_t st);
 
 // ---- tables / debug ----
 void launch_gauss_table(const sk_sketch *s, float *gtab, hipStream_t st);

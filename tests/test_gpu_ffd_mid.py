@@ -1,0 +1,44 @@
+"""FFD with 2^14 <= D <= 2^19 (row and column passes): every column-tile width, one to nine blocks (places on the
+XCDs beyond a multiple of 8), ragged ends of rows and blocks, several layers added into one output, one to five
+vectors in fp32 and bf16 at odd starts, theta0, and a small workspace (chunks of vectors), against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from test_gpu_parity import TOL_BF16, TOL_F32, dev, oracle_in, rand_inputs, rel_err  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(14, [(1, 9 * 2 ** 14 - 5), (1, 3)], 3, None), (15, [(1, 2 ** 15 + 1), (3, 5001)], 1, None),
+         (16, [(1, 5 * 2 ** 16 + 1025)], 5, None), (16, [(1, 8 * 2 ** 16)], 1, None),
+         (17, [(1, 2 ** 17 - 1023)], 2, None), (18, [(1, 2 ** 18 + 1024), (1, 7)], 1, None),
+         (19, [(1, 2 ** 19 + 2 ** 18 + 3)], 2, None), (16, [(1, 17 * 2 ** 16 + 3)], 5, 24)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_ffd_mid(case, dtype, dev, monkeypatch):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    lgD, shapes, batch, ws_mb = CASES[case]
+    if ws_mb is not None:
+        monkeypatch.setenv("SK_WORKSPACE_MB", str(ws_mb))
+    D, seed = 1 << lgD, 700 + case
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    s = Sketch("ffd", shapes, D, seed, device=dev)
+    xs = rand_inputs(shapes, batch, seed, dtype=tdt)
+    ref = O.apply("ffd", shapes, D, seed, [oracle_in(x)[0] for x in xs], dtype=dtype)
+    xd = [x.to(dev) for x in xs]
+    y = s.apply(xd)
+    assert rel_err(y.cpu().numpy(), ref) < TOL_F32
+    s.apply(xd, out=y, accumulate=True)
+    assert rel_err(y.cpu().numpy(), 2 * ref) < TOL_F32
+    g = torch.Generator().manual_seed(seed)
+    z = torch.randn((batch, D), generator=g)
+    th = [torch.randn(r * c, generator=g) * 0.02 if i % 2 == 0 else None for i, (r, c) in enumerate(shapes)]
+    outs = s.apply_T(z.to(dev), out_dtype=tdt, theta0=[None if t is None else t.to(dev) for t in th])
+    refs = O.apply_T("ffd", shapes, D, seed, z.numpy().astype(np.float64),
+                     theta0=[None if t is None else t.numpy() for t in th])
+    for o, r in zip(outs, refs):
+        assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL_F32)
+    s.close()
