@@ -1025,27 +1025,31 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
         }
         break;
       case SK_QK: {
-        std::vector<int> rest;  // layers off the bf16 tiling: fp64 sums, many layers per launch
-        for (int l = l0; l < l1; ++l) {
-          if (!qk_bf16_path(s->layers[l], dtype)) {
-            rest.push_back(l);
-            continue;
+        std::vector<int> bf, rest;  // on the bf16 tiling; off it: fp64 sums
+        for (int l = l0; l < l1; ++l) (qk_bf16_path(s->layers[l], dtype, bc) ? bf : rest).push_back(l);
+        auto bytes_of = [&](const int32_t *ls, int n, const void **x, int64_t &in, int64_t &ob) {
+          in = ob = 0;
+          for (int j = 0; j < n; ++j) {
+            const LayerDesc &ld = s->layers[ls[j]];
+            x[j] = grads[ls[j] - l0];
+            in += bc * ld.n * esz;
+            ob += bc * ld.da * ld.db * 4;
           }
-          SK_PROF(SK_PROF_QK_XB, bc * s->layers[l].n * esz,
-                  launch_qk_apply(s, l, grads[l - l0], dtype, b0, bc, s->ws, 1, out, accumulate != 0, st));
-          SK_PROF(SK_PROF_QK, bc * s->layers[l].da * s->layers[l].db * 4,
-                  launch_qk_apply(s, l, grads[l - l0], dtype, b0, bc, s->ws, 2, out, accumulate != 0, st));
+        };
+        for (size_t i = 0; i < bf.size();) {
+          const QkGroup g = qk_group(s, bf.data() + i, (int)(bf.size() - i), bc, s->ws_bytes);
+          const void *x[kQkTasks];
+          int64_t in_bytes, out_bytes;
+          bytes_of(g.layer, g.n, x, in_bytes, out_bytes);
+          SK_PROF(SK_PROF_QK_XB, in_bytes, launch_qk_first(s, g, x, b0, bc, s->ws, st));
+          SK_PROF(SK_PROF_QK, out_bytes, launch_qk_second(s, g, b0, bc, s->ws, out, accumulate != 0, st));
+          i += g.n;
         }
         for (size_t i = 0; i < rest.size();) {
           const Qk64Group g = qk64_group(s, rest.data() + i, (int)(rest.size() - i), bc, s->ws_bytes);
           const void *x[kQk64Tasks];
-          int64_t in_bytes = 0, out_bytes = 0;
-          for (int j = 0; j < g.n; ++j) {
-            const LayerDesc &ld = s->layers[g.layer[j]];
-            x[j] = grads[g.layer[j] - l0];
-            in_bytes += bc * ld.n * esz;
-            out_bytes += bc * ld.da * ld.db * 4;
-          }
+          int64_t in_bytes, out_bytes;
+          bytes_of(g.layer, g.n, x, in_bytes, out_bytes);
           SK_PROF(SK_PROF_QK_XB, in_bytes, launch_qk64_first(s, g, x, dtype, b0, bc, s->ws, st));
           SK_PROF(SK_PROF_QK, out_bytes, launch_qk64_second(s, g, b0, bc, s->ws, out, accumulate != 0, st));
           i += g.n;

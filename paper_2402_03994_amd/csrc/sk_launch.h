@@ -266,11 +266,46 @@ void run_ffd_large_T(const sk_sketch *s, int layer, const float *z, int64_t b_be
 
 // ---- QK ----
 void launch_qk_factors(const sk_sketch *s, hipStream_t st);
-// stages: bit 0 = T = X B^T (reads the gradients), bit 1 = out (+)= A T
-void launch_qk_apply(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc,
-                     float *t_ws, int stages, float *out, bool accumulate, hipStream_t st);
-// Does the layer take the bf16 matrix-core contractions of launch_qk_apply?  (Else: the fp64-sum ones below.)
-bool qk_bf16_path(const LayerDesc &ld, int dtype);
+// Does the layer take the bf16 matrix-core contractions in a call of bc vectors?  (Else: the fp64-sum ones below.)
+bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t bc);
+// Tasks of a launch, by value in the kernel arguments (under 4 KB).
+constexpr int kQkTasks = 32;
+struct QkFirstTask {
+  const uint16_t *x, *fh, *fl;  // input, factor as bf16 hi and lo terms
+  float *t;                     // T^T or U
+  int64_t m, n;
+  uint32_t blk0;                // first workgroup
+};
+struct QkFirst {
+  QkFirstTask t[kQkTasks];
+  int64_t bc;
+  int32_t n;
+};
+struct QkSecondTask {
+  const float *p, *q;
+  float *part;  // partial sums [range][vector][da db], or null (one range)
+  int64_t p_vs, q_vs, K, kper, col;
+  int32_t da, db, nk;
+  uint32_t blk0;
+};
+struct QkSecond {
+  QkSecondTask t[kQkTasks];
+  int64_t bc, D;
+  float *out;
+  int32_t n, accumulate;
+};
+struct QkGroup {  // layers of one set of launches; float offsets into the workspace
+  int32_t n;
+  int32_t layer[kQkTasks];
+  int64_t t_off[kQkTasks], spare;
+};
+// The next layers of the list whose intermediates for bc vectors fit the workspace together (at least one).
+QkGroup qk_group(const sk_sketch *s, const int *layers, int count, int64_t bc, int64_t ws_bytes);
+// x: one pointer per layer of the group
+void launch_qk_first(const sk_sketch *s, const QkGroup &g, const void *const *x, int64_t b_begin, int64_t bc, float *ws,
+                     hipStream_t st);
+void launch_qk_second(const sk_sketch *s, const QkGroup &g, int64_t b_begin, int64_t bc, float *ws, float *out,
+                      bool accumulate, hipStream_t st);
 
 // fp64-sum contractions (sk_qk64.hip): tasks of up to kQk64Tasks layers per launch, by value in the kernel
 // arguments (under 4 KB).

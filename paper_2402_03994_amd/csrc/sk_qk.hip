@@ -77,27 +77,44 @@ union Pack8 {
   bf16x8 v;
 };
 
+// Layers of a launch are tasks in the kernel arguments: one layer's contraction
+// leaves the chip idle up to some 30 vectors (48 workgroups for a 768 x 768
+// matrix and 16 vectors, and 45 us a layer whatever the batch).  12 GPT-2
+// blocks (60 matrices), one launch per layer and contraction against groups:
+// 2674 -> 591 us for 8 vectors, 3145 -> 1844 for 32; a 2048-wide decoder block,
+// 64 vectors: 1542 -> 1447.  Dividing one layer's contraction index instead
+// writes more partial products than it reads inputs (3741 for the 32).
+template <class Args>
+__device__ __forceinline__ const auto &qk_task(const Args &a) {
+  int i = 0;
+  while (i + 1 < a.n && blockIdx.x >= a.t[i + 1].blk0) ++i;
+  return a.t[i];
+}
+
 constexpr int kQkMR = 4;                  // 16-row tiles per wave
 constexpr int kQkRows = 4 * kQkMR * 16;   // stacked rows per workgroup (4 waves)
 constexpr int kQkBRow = 128 * 2 + 16;     // bytes of one B row chunk in LDS (padded)
 
 template <int NT>
-__global__ __launch_bounds__(256) void k_qk_s1(const uint16_t *__restrict__ x, const uint16_t *__restrict__ B,
-                                               const uint16_t *__restrict__ Blo, int64_t m, int64_t n,
-                                               int64_t b_begin, int64_t rows, float *__restrict__ tt) {
+__global__ __launch_bounds__(256) void k_qk_s1(QkFirst a) {
+  const QkFirstTask &task = qk_task(a);
+  const uint32_t blk = blockIdx.x - task.blk0;
+  const uint16_t *__restrict__ x = task.x, *__restrict__ B = task.fh, *__restrict__ Blo = task.fl;
+  float *__restrict__ tt = task.t;
+  const int64_t m = task.m, n = task.n, rows = a.bc * m;
   constexpr int DB = NT * 16;
   __shared__ __align__(16) unsigned char bs[2 * DB * kQkBRow];  // [hi|lo][row][128 bf16 + pad]
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int li = lane & 15, g = lane >> 4;
-  const int64_t r0 = (int64_t)blockIdx.x * kQkRows + wave * (kQkMR * 16);
+  const int64_t r0 = (int64_t)blk * kQkRows + wave * (kQkMR * 16);
   const uint16_t *xr[kQkMR];
   bool rv[kQkMR];
 #pragma unroll
   for (int mr = 0; mr < kQkMR; ++mr) {
     const int64_t row = r0 + mr * 16 + li;
     rv[mr] = row < rows;
-    xr[mr] = x + (b_begin * m + (rv[mr] ? row : 0)) * n + g * 8;
+    xr[mr] = x + (rv[mr] ? row : 0) * n + g * 8;
   }
   floatx4 acc[kQkMR][NT];
 #pragma unroll
@@ -108,12 +125,12 @@ __global__ __launch_bounds__(256) void k_qk_s1(const uint16_t *__restrict__ x, c
     // this wave's X fragments: MFMA cc takes k = k0 + 32 cc + 8 g .. + 7 in lane (li, g), so each load
     // instruction reads 64 contiguous bytes of each of 16 rows (16 cache lines, not 32 half-used ones:
     // the address units bound this loop)
-    Pack8 a[kQkMR][4];
+    Pack8 xf[kQkMR][4];
 #pragma unroll
     for (int mr = 0; mr < kQkMR; ++mr)
 #pragma unroll
       for (int cc = 0; cc < 4; ++cc)
-        a[mr][cc].u = rv[mr] ? *(const uint4 *)(xr[mr] + k0 + cc * 32) : make_uint4(0, 0, 0, 0);
+        xf[mr][cc].u = rv[mr] ? *(const uint4 *)(xr[mr] + k0 + cc * 32) : make_uint4(0, 0, 0, 0);
     __syncthreads();  // previous chunk of B consumed
     // B[hi|lo][row][k0 .. k0+127] -> LDS, 16 bytes per thread per step
     for (int e = threadIdx.x; e < 2 * DB * 16; e += 256) {
@@ -134,10 +151,10 @@ __global__ __launch_bounds__(256) void k_qk_s1(const uint16_t *__restrict__ x, c
         vl.u = *(const uint4 *)(bl + cc * 64);
 #pragma unroll
         for (int mr = 0; mr < kQkMR; ++mr)
-          acc[mr][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mr][cc].v, vh.v, acc[mr][t], 0, 0, 0);
+          acc[mr][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[mr][cc].v, vh.v, acc[mr][t], 0, 0, 0);
 #pragma unroll
         for (int mr = 0; mr < kQkMR; ++mr)
-          acc[mr][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mr][cc].v, vl.v, acc[mr][t], 0, 0, 0);
+          acc[mr][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[mr][cc].v, vl.v, acc[mr][t], 0, 0, 0);
       }
     }
   }
@@ -163,14 +180,18 @@ __global__ __launch_bounds__(256) void k_qk_s1(const uint16_t *__restrict__ x, c
 // next step's rows load during the current MFMAs.  Stage 2 is k_qk_s2 with U
 // per vector and B in fp32.
 template <int MT>
-__global__ __launch_bounds__(256) void k_qk_s1a(const uint16_t *__restrict__ x, const uint16_t *__restrict__ Ah,
-                                                const uint16_t *__restrict__ Al, int64_t m, int64_t n,
-                                                int64_t b_begin, float *__restrict__ u) {
+__global__ __launch_bounds__(256) void k_qk_s1a(QkFirst a) {
+  const QkFirstTask &task = qk_task(a);
+  const uint32_t blk = blockIdx.x - task.blk0;
+  const uint16_t *__restrict__ x = task.x, *__restrict__ Ah = task.fh, *__restrict__ Al = task.fl;
+  float *__restrict__ u = task.t;
+  const int64_t m = task.m, n = task.n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, g = lane >> 4;
-  const int64_t v = blockIdx.y;
-  const int64_t j0 = (int64_t)blockIdx.x * 256 + wave * 64 + 4 * li;  // this lane's four columns
-  const uint16_t *xc = x + (b_begin + v) * m * n + j0 + (int64_t)(g * 8) * n;
+  const uint32_t ncol = (uint32_t)(n / 256);
+  const int64_t v = blk / ncol;
+  const int64_t j0 = (int64_t)(blk % ncol) * 256 + wave * 64 + 4 * li;  // this lane's four columns
+  const uint16_t *xc = x + v * m * n + j0 + (int64_t)(g * 8) * n;
   const uint16_t *ah = Ah + (int64_t)li * m + g * 8;
   const uint16_t *al = Al + (int64_t)li * m + g * 8;
   floatx4 acc[MT][4];
@@ -229,8 +250,8 @@ __global__ __launch_bounds__(256) void k_qk_s1a(const uint16_t *__restrict__ x, 
   for (int t = 0; t < MT; ++t)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int64_t a = t * 16 + g * 4 + i;
-      *(float4 *)(ub + a * n) = make_float4(acc[t][0][i], acc[t][1][i], acc[t][2][i], acc[t][3][i]);
+      const int64_t row = t * 16 + g * 4 + i;
+      *(float4 *)(ub + row * n) = make_float4(acc[t][0][i], acc[t][1][i], acc[t][2][i], acc[t][3][i]);
     }
 }
 
@@ -239,14 +260,18 @@ __global__ __launch_bounds__(256) void k_qk_s1a(const uint16_t *__restrict__ x, 
 // 8-byte form for the same bytes), which gives eight 16-column sets per MFMA
 // group; steps of 32 rows, the next step's rows loading during the MFMAs.
 template <int MT>
-__global__ __launch_bounds__(256) void k_qk_s1aw(const uint16_t *__restrict__ x, const uint16_t *__restrict__ Ah,
-                                                 const uint16_t *__restrict__ Al, int64_t m, int64_t n,
-                                                 int64_t b_begin, float *__restrict__ u) {
+__global__ __launch_bounds__(256) void k_qk_s1aw(QkFirst a) {
+  const QkFirstTask &task = qk_task(a);
+  const uint32_t blk = blockIdx.x - task.blk0;
+  const uint16_t *__restrict__ x = task.x, *__restrict__ Ah = task.fh, *__restrict__ Al = task.fl;
+  float *__restrict__ u = task.t;
+  const int64_t m = task.m, n = task.n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, g = lane >> 4;
-  const int64_t v = blockIdx.y;
-  const int64_t j0 = (int64_t)blockIdx.x * 512 + wave * 128 + 8 * li;  // this lane's eight columns
-  const uint16_t *xc = x + (b_begin + v) * m * n + j0 + (int64_t)(g * 8) * n;
+  const uint32_t ncol = (uint32_t)(n / 512);
+  const int64_t v = blk / ncol;
+  const int64_t j0 = (int64_t)(blk % ncol) * 512 + wave * 128 + 8 * li;  // this lane's eight columns
+  const uint16_t *xc = x + v * m * n + j0 + (int64_t)(g * 8) * n;
   const uint16_t *ah = Ah + (int64_t)li * m + g * 8;
   const uint16_t *al = Al + (int64_t)li * m + g * 8;
   floatx4 acc[MT][8];
@@ -295,9 +320,9 @@ __global__ __launch_bounds__(256) void k_qk_s1aw(const uint16_t *__restrict__ x,
   for (int t = 0; t < MT; ++t)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int64_t a = t * 16 + g * 4 + i;
-      *(float4 *)(ub + a * n) = make_float4(acc[t][0][i], acc[t][1][i], acc[t][2][i], acc[t][3][i]);
-      *(float4 *)(ub + a * n + 4) = make_float4(acc[t][4][i], acc[t][5][i], acc[t][6][i], acc[t][7][i]);
+      const int64_t row = t * 16 + g * 4 + i;
+      *(float4 *)(ub + row * n) = make_float4(acc[t][0][i], acc[t][1][i], acc[t][2][i], acc[t][3][i]);
+      *(float4 *)(ub + row * n + 4) = make_float4(acc[t][4][i], acc[t][5][i], acc[t][6][i], acc[t][7][i]);
     }
 }
 
@@ -314,22 +339,31 @@ bool qk_afirst_ok(const LayerDesc &ld, int dtype) {
 // v_mfma_f32_16x16x4f32.  One workgroup per (vector, block of TA x TB output
 // tiles of 16 x 16): each wave keeps the TA x TB accumulators of the block over
 // a quarter of K, so every P and Q row is read once per workgroup, and the four
-// partial blocks are added in a fixed order through LDS.
+// partial blocks are added in a fixed order through LDS.  While the
+// blocks of a launch are few, K is divided into nk ranges (kper terms, a
+// multiple of 64) whose sums go to part[z][v][a db + c], added in order by
+// k_qk_s2_sum: 128 workgroups with 8192 terms each (fc2 of a 2048-wide decoder,
+// 64 vectors) took 110 us for 67 MB.
 template <int TA, int TB>
-__global__ __launch_bounds__(256) void k_qk_s2(const float *__restrict__ P, int64_t p_vs,
-                                               const float *__restrict__ Q, int64_t q_vs, int64_t K, int da, int db,
-                                               int64_t D, int64_t col, int64_t b_begin, float *__restrict__ out,
-                                               int accumulate) {
+__global__ __launch_bounds__(256) void k_qk_s2(QkSecond a) {
   __shared__ float red[4][TA * TB][64][4];
+  const QkSecondTask &task = qk_task(a);
+  const float *__restrict__ P = task.p, *__restrict__ Q = task.q;
+  const int64_t p_vs = task.p_vs, q_vs = task.q_vs, K = task.K, kper = task.kper;
+  const int da = task.da, db = task.db;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nbb = db / (16 * TB);
-  const int ba = blockIdx.x / nbb, bb = blockIdx.x - (blockIdx.x / nbb) * nbb;
-  const int64_t v = blockIdx.y;
+  const int nbb = db / (16 * TB), nb = da / (16 * TA) * nbb;
+  uint32_t e0 = blockIdx.x - task.blk0;
+  const int blk = (int)(e0 % (uint32_t)nb);
+  e0 /= (uint32_t)nb;
+  const int64_t v = e0 % (uint32_t)a.bc, z = e0 / (uint32_t)a.bc;
+  const int ba = blk / nbb, bb = blk - (blk / nbb) * nbb;
   const int li = lane & 15, g = lane >> 4;
   const float *pr = P + v * p_vs + (int64_t)(ba * TA * 16 + li) * K + g * 4;
   const float *qr = Q + v * q_vs + (int64_t)(bb * TB * 16 + li) * K + g * 4;
-  const int64_t per = ((K + 63) / 64) * 16;  // K range per wave, a multiple of 16
-  const int64_t kb = wave * per, ke = kb + per < K ? kb + per : K;
+  const int64_t z0 = z * kper, z1 = z0 + kper < K ? z0 + kper : K;
+  const int64_t per = ((z1 - z0 + 63) / 64) * 16;  // K range per wave, a multiple of 16
+  const int64_t kb = z0 + wave * per, ke = kb + per < z1 ? kb + per : z1;
   floatx4 acc[TA][TB];
 #pragma unroll
   for (int i = 0; i < TA; ++i)
@@ -413,92 +447,175 @@ __global__ __launch_bounds__(256) void k_qk_s2(const float *__restrict__ P, int6
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const float y = ((red[0][tile][ln][q] + red[1][tile][ln][q]) + red[2][tile][ln][q]) + red[3][tile][ln][q];
-      const int a = (ba * TA + i) * 16 + (ln >> 4) * 4 + q, c = (bb * TB + j) * 16 + (ln & 15);
-      float *o = out + (b_begin + v) * D + col + (int64_t)a * db + c;
-      *o = accumulate ? *o + y : y;
+      const int ra = (ba * TA + i) * 16 + (ln >> 4) * 4 + q, c = (bb * TB + j) * 16 + (ln & 15);
+      if (task.part) {
+        task.part[(z * a.bc + v) * ((int64_t)da * db) + (int64_t)ra * db + c] = y;
+      } else {
+        float *o = a.out + v * a.D + task.col + (int64_t)ra * db + c;
+        *o = a.accumulate ? *o + y : y;
+      }
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_qk_s2_sum(QkSecond a) {
+  const QkSecondTask &task = qk_task(a);
+  const int64_t cnt = (int64_t)task.da * task.db;
+  const int64_t e = (int64_t)(blockIdx.x - task.blk0) * 256 + threadIdx.x;
+  if (e >= cnt * a.bc) return;
+  float y = 0.0f;
+#pragma unroll 8
+  for (int z = 0; z < task.nk; ++z) y += task.part[(int64_t)z * a.bc * cnt + e];
+  const int64_t v = e / cnt;
+  float *o = a.out + v * a.D + task.col + (e - v * cnt);
+  *o = a.accumulate ? *o + y : y;
 }
 
 // Tiles per block along a side of n16 tiles: the largest of 4, 2, 1 dividing it.
 static int qk_block_tiles(int n16) { return n16 % 4 == 0 ? 4 : n16 % 2 == 0 ? 2 : 1; }
 
-static void launch_qk_s2(const float *P, int64_t p_vs, const float *Q, int64_t q_vs, int64_t K, int da, int db,
-                         int64_t D, int64_t col, int64_t b_begin, int64_t bc, float *out, bool accumulate,
-                         hipStream_t st) {
-  const int ta = qk_block_tiles(da / 16), tb = qk_block_tiles(db / 16);
-  const dim3 grid((unsigned)((da / (16 * ta)) * (db / (16 * tb))), (unsigned)bc);
-#define SK_S2(A, B)                                                                                      \
-  if (ta == A && tb == B)                                                                                \
-  hipLaunchKernelGGL((k_qk_s2<A, B>), grid, dim3(256), 0, st, P, p_vs, Q, q_vs, K, da, db, D, col, b_begin, out, \
-                     (int)accumulate)
-  SK_S2(1, 1); SK_S2(1, 2); SK_S2(1, 4); SK_S2(2, 1); SK_S2(2, 2); SK_S2(2, 4); SK_S2(4, 1); SK_S2(4, 2); SK_S2(4, 4);
-#undef SK_S2
-}
-
 bool qk_mfma_ok(const LayerDesc &ld, int dtype) {
   return dtype == SK_BF16 && ld.nc % 128 == 0 && ld.m % 16 == 0 && ld.da % 16 == 0 && ld.db % 16 == 0 && ld.db <= 128;
 }
 
-bool qk_bf16_path(const LayerDesc &ld, int dtype) { return qk_afirst_ok(ld, dtype) || qk_mfma_ok(ld, dtype); }
+// One vector goes through the fp64-sum kernels: their workgroups split the
+// contraction over four waves, and the length of one chain is what counts (12
+// GPT-2 blocks of width 768: 270 against 377 us; 2048-wide decoder block 125
+// against 172; two vectors 400 against 443, 163 against 175, but 181 against 131
+// for four blocks of width 1024).
+bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t bc) {
+  return bc > 1 && (qk_afirst_ok(ld, dtype) || qk_mfma_ok(ld, dtype));
+}
 
-void launch_qk_apply(const sk_sketch *s, int layer, const void *x, int dtype, int64_t b_begin, int64_t bc,
-                     float *t_ws, int stages, float *out, bool accumulate, hipStream_t st) {
-  const LayerDesc &ld = s->layers[layer];
-  const float *A = s->d_qka + ld.fa_off;
-  const uint16_t *B = s->d_qkb + ld.fb_off, *Blo = s->d_qkb + s->qk_b_elems + ld.fb_off;
-  if (qk_afirst_ok(ld, dtype)) {
-    if (stages & 1) {
-      const uint16_t *Ah = s->d_qkah + ld.fa_off, *Al = s->d_qkah + s->qk_a_elems + ld.fa_off;
-      const dim3 g1((unsigned)(ld.nc / 256), (unsigned)bc);
-      if (ld.nc % 512 == 0 && ld.da <= 32) {
-        // eight columns per lane (16-byte loads)
-        const dim3 g1w((unsigned)(ld.nc / 512), (unsigned)bc);
-        if (ld.da == 16)
-          hipLaunchKernelGGL(k_qk_s1aw<1>, g1w, dim3(256), 0, st, (const uint16_t *)x, Ah, Al, (int64_t)ld.m,
-                             (int64_t)ld.nc, b_begin, t_ws);
-        else
-          hipLaunchKernelGGL(k_qk_s1aw<2>, g1w, dim3(256), 0, st, (const uint16_t *)x, Ah, Al, (int64_t)ld.m,
-                             (int64_t)ld.nc, b_begin, t_ws);
-      } else switch (ld.da / 16) {
-        case 1: hipLaunchKernelGGL(k_qk_s1a<1>, g1, dim3(256), 0, st, (const uint16_t *)x, Ah, Al, (int64_t)ld.m,
-                                   (int64_t)ld.nc, b_begin, t_ws); break;
-        case 2: hipLaunchKernelGGL(k_qk_s1a<2>, g1, dim3(256), 0, st, (const uint16_t *)x, Ah, Al, (int64_t)ld.m,
-                                   (int64_t)ld.nc, b_begin, t_ws); break;
-        case 3: hipLaunchKernelGGL(k_qk_s1a<3>, g1, dim3(256), 0, st, (const uint16_t *)x, Ah, Al, (int64_t)ld.m,
-                                   (int64_t)ld.nc, b_begin, t_ws); break;
-        default: hipLaunchKernelGGL(k_qk_s1a<4>, g1, dim3(256), 0, st, (const uint16_t *)x, Ah, Al, (int64_t)ld.m,
-                                    (int64_t)ld.nc, b_begin, t_ws); break;
+QkGroup qk_group(const sk_sketch *s, const int *layers, int count, int64_t bc, int64_t ws_bytes) {
+  QkGroup g{};
+  int64_t off = 0;
+  while (g.n < count && g.n < kQkTasks) {
+    const LayerDesc &ld = s->layers[layers[g.n]];
+    const int64_t need = bc * (qk_afirst_ok(ld, SK_BF16) ? (int64_t)ld.da * ld.nc : (int64_t)ld.m * ld.db);
+    if (g.n && (off + need) * 4 > ws_bytes) break;
+    g.layer[g.n] = layers[g.n];
+    g.t_off[g.n] = off;
+    off += (need + 3) & ~3ll;
+    ++g.n;
+  }
+  g.spare = off;
+  return g;
+}
+
+void launch_qk_first(const sk_sketch *s, const QkGroup &g, const void *const *x, int64_t b_begin, int64_t bc, float *ws,
+                     hipStream_t st) {
+  // one launch per kernel: 0-7 B first with 1-8 tiles of B, 8-11 A first with 1-4 tiles of A, 12-13 its wide form
+  for (int cls = 0; cls < 14; ++cls) {
+    QkFirst a{};
+    a.bc = bc;
+    int64_t blk = 0;
+    for (int i = 0; i < g.n; ++i) {
+      const LayerDesc &ld = s->layers[g.layer[i]];
+      const bool af = qk_afirst_ok(ld, SK_BF16), wide = ld.nc % 512 == 0 && ld.da <= 32;
+      if (cls != (!af ? ld.db / 16 - 1 : (wide ? 12 : 8) + ld.da / 16 - 1)) continue;
+      QkFirstTask &t = a.t[a.n++];
+      t.x = (const uint16_t *)x[i] + b_begin * ld.m * ld.nc;
+      t.fh = af ? s->d_qkah + ld.fa_off : s->d_qkb + ld.fb_off;
+      t.fl = t.fh + (af ? s->qk_a_elems : s->qk_b_elems);
+      t.t = ws + g.t_off[i];
+      t.m = ld.m;
+      t.n = ld.nc;
+      t.blk0 = (uint32_t)blk;
+      blk += !af ? (bc * ld.m + kQkRows - 1) / kQkRows : bc * (ld.nc / (wide ? 512 : 256));
+    }
+    if (!a.n) continue;
+    const dim3 grid((unsigned)blk);
+    switch (cls) {
+      case 0: hipLaunchKernelGGL(k_qk_s1<1>, grid, dim3(256), 0, st, a); break;
+      case 1: hipLaunchKernelGGL(k_qk_s1<2>, grid, dim3(256), 0, st, a); break;
+      case 2: hipLaunchKernelGGL(k_qk_s1<3>, grid, dim3(256), 0, st, a); break;
+      case 3: hipLaunchKernelGGL(k_qk_s1<4>, grid, dim3(256), 0, st, a); break;
+      case 4: hipLaunchKernelGGL(k_qk_s1<5>, grid, dim3(256), 0, st, a); break;
+      case 5: hipLaunchKernelGGL(k_qk_s1<6>, grid, dim3(256), 0, st, a); break;
+      case 6: hipLaunchKernelGGL(k_qk_s1<7>, grid, dim3(256), 0, st, a); break;
+      case 7: hipLaunchKernelGGL(k_qk_s1<8>, grid, dim3(256), 0, st, a); break;
+      case 8: hipLaunchKernelGGL(k_qk_s1a<1>, grid, dim3(256), 0, st, a); break;
+      case 9: hipLaunchKernelGGL(k_qk_s1a<2>, grid, dim3(256), 0, st, a); break;
+      case 10: hipLaunchKernelGGL(k_qk_s1a<3>, grid, dim3(256), 0, st, a); break;
+      case 11: hipLaunchKernelGGL(k_qk_s1a<4>, grid, dim3(256), 0, st, a); break;
+      case 12: hipLaunchKernelGGL(k_qk_s1aw<1>, grid, dim3(256), 0, st, a); break;
+      default: hipLaunchKernelGGL(k_qk_s1aw<2>, grid, dim3(256), 0, st, a); break;
+    }
+  }
+}
+
+void launch_qk_second(const sk_sketch *s, const QkGroup &g, int64_t b_begin, int64_t bc, float *ws, float *out,
+                      bool accumulate, hipStream_t st) {
+  QkSecond sum{};
+  sum.bc = bc;
+  sum.D = s->D;
+  sum.out = out + b_begin * s->D;
+  sum.accumulate = accumulate;
+  int64_t total = 0, sblk = 0, spare = g.spare;  // output blocks of the group; floats taken
+  for (int i = 0; i < g.n; ++i) {
+    const LayerDesc &ld = s->layers[g.layer[i]];
+    total += bc * (ld.da / (16 * qk_block_tiles(ld.da / 16))) * (ld.db / (16 * qk_block_tiles(ld.db / 16)));
+  }
+  for (int cls = 0; cls < 9; ++cls) {  // (1, 2, 4) x (1, 2, 4) tiles per block
+    const int ta = 1 << cls / 3, tb = 1 << cls % 3;
+    QkSecond a = sum;
+    a.n = 0;
+    int64_t blk = 0;
+    for (int i = 0; i < g.n; ++i) {
+      const LayerDesc &ld = s->layers[g.layer[i]];
+      if (qk_block_tiles(ld.da / 16) != ta || qk_block_tiles(ld.db / 16) != tb) continue;
+      const float *im = ws + g.t_off[i];
+      QkSecondTask &t = a.t[a.n++];
+      t = QkSecondTask{};
+      if (qk_afirst_ok(ld, SK_BF16)) {  // Y[v][a][c] = sum_j U[v][a][j] B[c][j]
+        t.p = im;
+        t.p_vs = (int64_t)ld.da * ld.nc;
+        t.q = s->d_qkbf + ld.fb_off;
+        t.K = ld.nc;
+      } else {  // Y[v][a][c] = sum_i A[a][i] T^T[v][c][i]
+        t.p = s->d_qka + ld.fa_off;
+        t.q = im;
+        t.q_vs = (int64_t)ld.db * ld.m;
+        t.K = ld.m;
+      }
+      t.da = ld.da;
+      t.db = ld.db;
+      t.col = ld.qk_col;
+      // ranges of K: 1024 workgroups in the group (four per CU), 512 terms or more each, as far as the partial
+      // sums fit
+      const int64_t cnt = (int64_t)ld.da * ld.db;
+      int64_t nk = std::min({t.K / 512, 1024 / total, (s->ws_bytes / 4 - spare) / (bc * cnt)});
+      if (nk < 2) nk = 1;
+      t.kper = ((t.K + nk - 1) / nk + 63) / 64 * 64;
+      nk = (t.K + t.kper - 1) / t.kper;
+      t.nk = (int)nk;
+      t.blk0 = (uint32_t)blk;
+      blk += (ld.da / (16 * ta)) * (ld.db / (16 * tb)) * bc * nk;
+      if (nk > 1) {
+        t.part = ws + spare;
+        spare += nk * bc * cnt;
+        QkSecondTask &u = sum.t[sum.n++];
+        u = t;
+        u.blk0 = (uint32_t)sblk;
+        sblk += (bc * cnt + 255) / 256;
       }
     }
-    if (stages & 2) {
-      // Y[v][a][c] = sum_j U[v][a][j] B[c][j]
-      launch_qk_s2(t_ws, (int64_t)ld.da * ld.nc, s->d_qkbf + ld.fb_off, 0, (int64_t)ld.nc, ld.da, ld.db, s->D,
-                   ld.qk_col, b_begin, bc, out, accumulate, st);
+    if (!a.n) continue;
+    const dim3 grid((unsigned)blk);
+    switch (cls) {
+      case 0: hipLaunchKernelGGL((k_qk_s2<1, 1>), grid, dim3(256), 0, st, a); break;
+      case 1: hipLaunchKernelGGL((k_qk_s2<1, 2>), grid, dim3(256), 0, st, a); break;
+      case 2: hipLaunchKernelGGL((k_qk_s2<1, 4>), grid, dim3(256), 0, st, a); break;
+      case 3: hipLaunchKernelGGL((k_qk_s2<2, 1>), grid, dim3(256), 0, st, a); break;
+      case 4: hipLaunchKernelGGL((k_qk_s2<2, 2>), grid, dim3(256), 0, st, a); break;
+      case 5: hipLaunchKernelGGL((k_qk_s2<2, 4>), grid, dim3(256), 0, st, a); break;
+      case 6: hipLaunchKernelGGL((k_qk_s2<4, 1>), grid, dim3(256), 0, st, a); break;
+      case 7: hipLaunchKernelGGL((k_qk_s2<4, 2>), grid, dim3(256), 0, st, a); break;
+      default: hipLaunchKernelGGL((k_qk_s2<4, 4>), grid, dim3(256), 0, st, a); break;
     }
-    (void)hipGetLastError();
-    return;
   }
-  const int64_t rows = bc * (int64_t)ld.m;
-  dim3 g1((unsigned)((rows + kQkRows - 1) / kQkRows));
-  if (stages & 1) {
-#define SK_S1(NT)                                                                                              \
-case NT:                                                                                                     \
-  hipLaunchKernelGGL(k_qk_s1<NT>, g1, dim3(256), 0, st, (const uint16_t *)x, B, Blo, (int64_t)ld.m,           \
-                     (int64_t)ld.nc,                                                                         \
-                     b_begin, rows, t_ws);                                                                   \
-  break;
-  switch (ld.db / 16) {
-    SK_S1(1) SK_S1(2) SK_S1(3) SK_S1(4) SK_S1(5) SK_S1(6) SK_S1(7) SK_S1(8)
-    default: break;
-  }
-#undef SK_S1
-  }
-  if (stages & 2) {
-    launch_qk_s2(A, 0, t_ws, (int64_t)ld.db * ld.m, (int64_t)ld.m, ld.da, ld.db, s->D, ld.qk_col, b_begin, bc, out,
-                 accumulate, st);
-  }
-  (void)hipGetLastError();
+  if (sum.n) hipLaunchKernelGGL(k_qk_s2_sum, dim3((unsigned)sblk), dim3(256), 0, st, sum);
 }
 
 }  // namespace sk
