@@ -20,7 +20,8 @@
 // vector's matrix is 2 to 10 us of work, and 146 launches in a row for the 73
 // matrices of GPT-2 small cost more than that.  Against one thread per output
 // looping over k with fp64 FMAs (uncoalesced rows, no reuse of a row), an
-// S^T z plus S x over those 73 matrices went from 54.2 ms to 0.98 ms.
+// S^T z plus S x over those 73 matrices went from 54.2 ms to 0.80 ms (0.98 with each
+// step's loads waited for before its products).
 #include <algorithm>
 
 #include "sk_launch.h"
@@ -97,17 +98,20 @@ __device__ __forceinline__ void qk64_dot(const Qk64Dot &t, int bp, int bq, int k
   for (int i = 0; i < TP; ++i)
 #pragma unroll
     for (int j = 0; j < TQ; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
-  constexpr int U = TP * TQ <= 2 ? 4 : 2;  // steps whose loads are in flight together
-  for (; k + 16 * U <= k1; k += 16 * U) {
-    floatx4u pv[U][TP];
-    typename E::V qv[U][TQ];
+  // U steps of 16 per buffer, the next buffer's loads in flight during the products
+  constexpr int U = TP == 1 ? 4 : TP == 2 ? 2 : 1;
+  floatx4u pv[2][U][TP];
+  typename E::V qv[2][U][TQ];
+  auto load = [&](int64_t kk, floatx4u(&p)[U][TP], typename E::V(&q)[U][TQ]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
-      for (int j = 0; j < TQ; ++j) qv[u][j] = *(const typename E::V *)(qr[j] + k + 16 * u);
+      for (int j = 0; j < TQ; ++j) q[u][j] = *(const typename E::V *)(qr[j] + kk + 16 * u);
 #pragma unroll
-      for (int i = 0; i < TP; ++i) pv[u][i] = *(const floatx4u *)(pr[i] + k + 16 * u);
+      for (int i = 0; i < TP; ++i) p[u][i] = *(const floatx4u *)(pr[i] + kk + 16 * u);
     }
+  };
+  auto products = [&](const floatx4u(&p)[U][TP], const typename E::V(&q)[U][TQ]) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -115,7 +119,22 @@ __device__ __forceinline__ void qk64_dot(const Qk64Dot &t, int bp, int bq, int k
 #pragma unroll
         for (int i = 0; i < TP; ++i)
 #pragma unroll
-          for (int j = 0; j < TQ; ++j) acc[i][j] = mfma((double)pv[u][i][s], E::at(qv[u][j], s), acc[i][j]);
+          for (int j = 0; j < TQ; ++j) acc[i][j] = mfma((double)p[u][i][s], E::at(q[u][j], s), acc[i][j]);
+  };
+  if (k + 16 * U <= k1) {
+    load(k, pv[0], qv[0]);
+    for (;;) {
+      k += 16 * U;
+      const bool more = k + 16 * U <= k1;  // uniform over the wave
+      if (more) load(k, pv[1], qv[1]);
+      products(pv[0], qv[0]);
+      if (!more) break;
+      k += 16 * U;
+      const bool more2 = k + 16 * U <= k1;
+      if (more2) load(k, pv[0], qv[0]);
+      products(pv[1], qv[1]);
+      if (!more2) break;
+    }
   }
   for (; k < k1; k += 16) {  // the last steps, guarded at the end of the range
 #pragma unroll
@@ -174,7 +193,7 @@ __device__ __forceinline__ void qk64_dot(const Qk64Dot &t, int bp, int bq, int k
 }
 
 template <bool QB>
-__global__ __launch_bounds__(256) void k_qk64_dot(Qk64DotArgs a) {
+__global__ __launch_bounds__(256, 3) void k_qk64_dot(Qk64DotArgs a) {
   __shared__ double red[2][8][4][64];
   int ti = 0;
   while (ti + 1 < a.n && blockIdx.x >= a.blk0[ti + 1]) ++ti;
@@ -245,37 +264,54 @@ __device__ __forceinline__ void qk64_outer(const Qk64Outer &t, int bm, int64_t b
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[i][c] = doublex4{0.0, 0.0, 0.0, 0.0};
-  // one step of 16 with every load issued before the first product
-  for (; k + 16 <= k1; k += 16) {
-    typename E::V qv[4];
-    float pv[TM][4];
+  // one step of 16 per buffer, the next step's loads in flight during the products
+  typename E::V qv[2][4];
+  float pv[2][TM][4];
+  auto load = [&](int64_t kk, typename E::V(&qb)[4], float(&pb)[TM][4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const typename E::T *qs = q + (k + 4 * g + s) * t.N;
+      const typename E::T *qs = q + (kk + 4 * g + s) * t.N;
       if (full) {
-        qv[s] = *(const typename E::V *)qs;
+        qb[s] = *(const typename E::V *)qs;
       } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) qv[s][c] = j0 + c < t.N ? qs[c] : (typename E::T)0;
+        for (int c = 0; c < 4; ++c) qb[s][c] = j0 + c < t.N ? qs[c] : (typename E::T)0;
       }
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       if (PK) {
-        const floatx4u x = *(const floatx4u *)(p[i] + k + 4 * g);
+        const floatx4u x = *(const floatx4u *)(p[i] + kk + 4 * g);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) pv[i][s] = x[s];
+        for (int s = 0; s < 4; ++s) pb[i][s] = x[s];
       } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) pv[i][s] = p[i][(k + 4 * g + s) * t.psk];
+        for (int s = 0; s < 4; ++s) pb[i][s] = p[i][(kk + 4 * g + s) * t.psk];
       }
     }
+  };
+  auto products = [&](const typename E::V(&qb)[4], const float(&pb)[TM][4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[i][c] = mfma((double)pv[i][s], E::at(qv[s], c), acc[i][c]);
+        for (int c = 0; c < 4; ++c) acc[i][c] = mfma((double)pb[i][s], E::at(qb[s], c), acc[i][c]);
+  };
+  if (k + 16 <= k1) {
+    load(k, qv[0], pv[0]);
+    for (;;) {
+      k += 16;
+      const bool more = k + 16 <= k1;
+      if (more) load(k, qv[1], pv[1]);
+      products(qv[0], pv[0]);
+      if (!more) break;
+      k += 16;
+      const bool more2 = k + 16 <= k1;
+      if (more2) load(k, qv[0], pv[0]);
+      products(qv[1], pv[1]);
+      if (!more2) break;
+    }
   }
   if (k < k1) {  // ragged end of the range
 #pragma unroll
@@ -372,7 +408,7 @@ __device__ __forceinline__ void qk64_outer(const Qk64Outer &t, int bm, int64_t b
 }
 
 template <bool KS, bool QB>
-__global__ __launch_bounds__(256) void k_qk64_outer(Qk64OuterArgs a) {
+__global__ __launch_bounds__(256, 3) void k_qk64_outer(Qk64OuterArgs a) {
   __shared__ double red[KS ? 2 : 1][8][4][64];
   int ti = 0;
   while (ti + 1 < a.n && blockIdx.x >= a.blk0[ti + 1]) ++ti;
