@@ -1120,6 +1120,11 @@ int sketch_apply_T(sk_sketch *s, const float *z, int64_t batch, void *const *out
           g.tile0[i + 1] = g.tile0[i] + (ld.rows_live + kAfjlTRows - 1) / kAfjlTRows;
           obytes += bc * ld.n * osz + (g.th[i] ? ld.n * 4 : 0);
         }
+        if (s->D >= 1024) {
+          SK_PROF(SK_PROF_PROLOG, bc * s->D * 4, run_afjl_T(s, g, ng, z, s->ws, b0, bc, out_dtype, 1, st));
+          SK_PROF(SK_PROF_GATHER, obytes, run_afjl_T(s, g, ng, z, s->ws, b0, bc, out_dtype, 2, st));
+          continue;
+        }
         SK_PROF(SK_PROF_PROLOG, bc * s->D * 4, launch_afjl_T_prep(s, la, ng, z, b0, bc, s->ws, st));
         SK_PROF(SK_PROF_FWHT, 0, fwht_inplace(s->ws, (int64_t)ng * bc, lgD, st));
         SK_PROF(SK_PROF_GATHER, obytes, launch_afjl_T_out(s, g, ng, s->ws, b0, bc, out_dtype, st));

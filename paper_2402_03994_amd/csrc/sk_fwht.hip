@@ -892,6 +892,206 @@ void launch_afjl_T_out(const sk_sketch *s, const AfjlTGroup &g, int ng, const fl
   SK_CHECK_LAUNCH();
 }
 
+// The same for D >= 1024 (every layer has L = Lw = 1024): H_D = H_R (x) H_1024
+// with the two halves where their data is.  k_afjl_T_cols forms g_l . z and H_R
+// along a column in registers (R <= 64; above, k_afjl_T_prep and column passes),
+// and the output kernel takes the fold's items backwards: one destination row r
+// of V = H_D(g_l . z) serves every source row h with pi1_{K-2}(h) mod R = r, so a
+// workgroup transforms that row of its (up to BT) vectors in LDS, keeps the four
+// entries per thread that pi1_{K-1} gives its columns in registers, and streams
+// up to kUnfoldRows output rows with their signs and theta0: no gather per
+// output (k_afjl_T_out: 2.4 TB/s of writes on 0.5 GB, one vector of GPT-2 small
+// at D = 2^16; 4.7 here: S H S^T 994 -> 769 us), and the row transform no longer passes through memory.
+template <int R>
+__global__ __launch_bounds__(256) void k_afjl_T_cols(const float *__restrict__ gtab, int l_first,
+                                                     const float *__restrict__ z, int64_t D, int64_t bc,
+                                                     int64_t b_begin, int64_t total, float *__restrict__ w) {
+  constexpr int H = R > 32 ? 2 : 1, J = R / H;
+  const int64_t gid = blockIdx.x * (int64_t)256 + threadIdx.x;
+  int c, h;
+  int64_t u;  // layer of the group x vector
+  if (H == 1) {
+    c = (int)(gid & 1023);
+    u = gid >> 10;
+    h = 0;
+  } else {  // the halves of a wave hold rows 32 h + j of its 32 columns
+    const int64_t wv = gid >> 6;
+    c = (int)(wv & 31) * 32 + (int)(threadIdx.x & 31);
+    u = wv >> 5;
+    h = (int)((threadIdx.x >> 5) & 1);
+  }
+  if (u >= total) return;  // uniform over a wave
+  const int64_t gl = u / bc, v = u - gl * bc;
+  const int64_t at = (int64_t)h * J * 1024 + c;
+  const float *gp = gtab + (l_first + gl) * D + at, *zp = z + (b_begin + v) * D + at;
+  float x[J], g[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) x[j] = zp[j * 1024];
+#pragma unroll
+  for (int j = 0; j < J; ++j) g[j] = gp[j * 1024];
+#pragma unroll
+  for (int j = 0; j < J; ++j) x[j] *= g[j];
+  fwht_regs_t<J>(x);
+  if (H == 2) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const float o = __shfl_xor(x[j], 32);
+      x[j] = h ? o - x[j] : x[j] + o;
+    }
+  }
+  const float sc = rsqrtf((float)R);
+  float *o = w + u * D + at;
+#pragma unroll
+  for (int j = 0; j < J; ++j) o[j * 1024] = x[j] * sc;
+}
+
+constexpr int kUnfoldRows = 64;  // source rows of one workgroup
+template <int BT>
+__global__ __launch_bounds__(256) void k_afjl_unfold(const FoldItem *__restrict__ items,
+                                                     const LayerDesc *__restrict__ layers,
+                                                     const uint16_t *__restrict__ ptab, AfjlTGroup g, int item_begin,
+                                                     int R, const float *__restrict__ w, int64_t D, int64_t bc,
+                                                     int64_t b_begin, int out_dtype, Key key) {
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  typedef uint16_t h4u __attribute__((ext_vector_type(4), aligned(2)));
+  using L8 = Lds1024<8>;
+  __shared__ __align__(16) float s[BT == 1 ? p16_floats(1024) : L8::kFloats];
+  __shared__ int32_t srow[kUnfoldRows];
+  __shared__ __align__(16) uint32_t sgn[kUnfoldRows * 32];
+  const FoldItem it = items[item_begin + blockIdx.x];
+  const int t0 = it.t0 + (int)blockIdx.z * kUnfoldRows;
+  const int nt = min(it.t1 - t0, kUnfoldRows);
+  if (nt <= 0) return;  // uniform
+  const LayerDesc &ld = layers[it.layer];
+  const int gl = it.layer - g.layer[0];
+  const int64_t v0 = (int64_t)blockIdx.y * BT;
+  const int nv = (int)(bc - v0 < BT ? bc - v0 : BT);
+  const int tid = threadIdx.x;
+  const float *wr = w + (gl * bc + v0) * D + (int64_t)it.r * 1024;
+  // the row of every vector on its way while the source rows and signs are made
+  float e[BT == 1 ? 4 : 32];
+  if (BT == 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) e[k] = wr[tid + 256 * k];
+  } else {
+    const float *p = wr + (int64_t)(tid >> 5 < nv ? tid >> 5 : 0) * D + (tid & 31);
+#pragma unroll
+    for (int k = 0; k < 32; ++k) e[k] = p[32 * k];
+  }
+  if (tid < nt) {
+    const int t = t0 + tid, nk = R > 1 ? ld.dk1 / R : 1;
+    const int htop = t / nk;
+    const int64_t h = R == 1 ? t : (int64_t)htop * ld.dk1 + ptab[ld.poff[0][1][ld.K - 2] + it.r + (t - htop * nk) * R];
+    srow[tid] = h < ld.rows_live ? (int32_t)h : -1;
+  }
+  const uint16_t *fk = ptab + ld.poff[0][0][ld.K - 1] + 4 * tid;
+  int idx[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) idx[q] = fk[q];
+  __syncthreads();
+  for (int u = tid; u < nt * 8; u += 256) {  // one Philox block per 128 coordinates
+    const int32_t h = srow[u >> 3];
+    if (h >= 0) {
+      const W4 wd = philox((uint64_t)h * 8u + (uint64_t)(u & 7), (uint32_t)ld.layer_id, ST_SIGN, key);
+      *reinterpret_cast<uint4 *>(&sgn[4 * u]) = make_uint4(wd.w[0], wd.w[1], wd.w[2], wd.w[3]);
+    }
+  }
+  float o[BT][4];
+  if (BT == 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[p16(tid + 256 * k)] = e[k];
+    lds_fwht_regs(s, 10, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[0][q] = s[p16(idx[q])] * (1.0f / 32.0f);
+  } else {
+    if constexpr (BT > 1) fwht1024_lds_regs<8>(s, e);
+#pragma unroll
+    for (int v = 0; v < BT; ++v)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[v][q] = s[L8::idx(v, idx[q])] * (1.0f / 32.0f);
+  }
+  const float *theta0 = g.th[gl];
+  void *out = g.out[gl];
+#pragma unroll 4
+  for (int i = 0; i < nt; ++i) {
+    const int32_t h = srow[i];
+    const int64_t j = (int64_t)h * 1024 + 4 * tid, lim = ld.n - j;
+    if (h < 0 || lim <= 0) continue;
+    const uint32_t bits = sgn[i * 32 + (tid >> 3)] >> ((4 * tid) & 31);
+    float th[4] = {0.f, 0.f, 0.f, 0.f};
+    if (theta0) {
+      if (lim >= 4) {
+        const f4u t = *reinterpret_cast<const f4u *>(theta0 + j);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) th[q] = t[q];
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < lim) th[q] = theta0[j + q];
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < BT; ++v) {
+      if (v >= nv) break;
+      float y[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = flip(o[v][q], (bits >> q) & 1u) + th[q];
+      const int64_t pos = (b_begin + v0 + v) * ld.n + j;
+      if (lim < 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < lim) store_out(out, out_dtype, pos + q, y[q]);
+      } else if (out_dtype == SK_BF16) {
+        h4u b;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) b[q] = f32_to_bf16(y[q]);
+        *reinterpret_cast<h4u *>((uint16_t *)out + pos) = b;
+      } else {
+        *reinterpret_cast<f4u *>((float *)out + pos) = f4u{y[0], y[1], y[2], y[3]};
+      }
+    }
+  }
+}
+
+void run_afjl_T(const sk_sketch *s, const AfjlTGroup &g, int ng, const float *z, float *w, int64_t b_begin, int64_t bc,
+                int out_dtype, int phases, hipStream_t st) {
+  const int la = g.layer[0], R = s->R;
+  if (phases & 1) {
+    const int64_t total = ng * bc;
+    const dim3 grid((unsigned)((total * 1024 * (R > 32 ? 2 : 1) + 255) / 256));
+#define SK_TCOLS(RR)                                                                                                \
+  case RR:                                                                                                          \
+    hipLaunchKernelGGL(k_afjl_T_cols<RR>, grid, dim3(256), 0, st, s->d_gtab, la, z, s->D, bc, b_begin, total, w);   \
+    break;
+    switch (R) {
+      SK_TCOLS(1) SK_TCOLS(2) SK_TCOLS(4) SK_TCOLS(8) SK_TCOLS(16) SK_TCOLS(32) SK_TCOLS(64)
+      default:
+        launch_afjl_T_prep(s, la, ng, z, b_begin, bc, w, st);
+        fwht_inplace_from(w, total, log2_exact(s->D), 10, st);
+        break;
+    }
+#undef SK_TCOLS
+  }
+  if (phases & 2) {
+    const LayerDesc &l1 = s->layers[la + ng - 1];
+    const int it0 = s->layers[la].item_off, it1 = l1.item_off + l1.n_items;
+    int64_t most = 1;  // rows of the longest item
+    for (int l = la; l < la + ng; ++l) {
+      const LayerDesc &ld = s->layers[l];
+      const int64_t t = R == 1 ? ld.rows_live : (ld.rows_live + ld.dk1 - 1) / ld.dk1 * (ld.dk1 / R);
+      most = std::max(most, std::min<int64_t>(t, kFoldRowsPerItem));
+    }
+    const unsigned gz = (unsigned)((most + kUnfoldRows - 1) / kUnfoldRows);
+    if (bc == 1)
+      hipLaunchKernelGGL(k_afjl_unfold<1>, dim3((unsigned)(it1 - it0), 1u, gz), dim3(256), 0, st, s->d_items,
+                         s->d_layers, s->d_ptab, g, it0, R, w, s->D, bc, b_begin, out_dtype, s->key);
+    else
+      hipLaunchKernelGGL(k_afjl_unfold<8>, dim3((unsigned)(it1 - it0), (unsigned)((bc + 7) / 8), gz), dim3(256), 0, st,
+                         s->d_items, s->d_layers, s->d_ptab, g, it0, R, w, s->D, bc, b_begin, out_dtype, s->key);
+  }
+  SK_CHECK_LAUNCH();
+}
+
 // ===========================================================================
 // AFFD.  w = Scatter_pi1(B x) is written in full (padded rows as zeros) by a
 // row kernel that reads source row pi1^{-1}(row) of x; then H_N' (generic

@@ -100,6 +100,10 @@ void launch_afjl_T_prep(const sk_sketch *s, int l_first, int ng, const float *z,
 void launch_afjl_T_out(const sk_sketch *s, const AfjlTGroup &g, int ng, const float *w, int64_t b_begin, int64_t bc,
                        int out_dtype, hipStream_t st);
 
+// The same for D >= 1024, into and from the same buffer w; phases: bit 0 = w, bit 1 = the outputs.
+void run_afjl_T(const sk_sketch *s, const AfjlTGroup &g, int ng, const float *z, float *w, int64_t b_begin, int64_t bc,
+                int out_dtype, int phases, hipStream_t st);
+
 // ---- AFFD ----
 // AFFD specialised for D > 1024, last digit 1024 and at most 64 top-digit values.
 bool affd_fast_path(const sk_sketch *s, int layer);

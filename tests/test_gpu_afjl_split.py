@@ -1,11 +1,13 @@
-"""AFJL calls whose fold items are split over several workgroups (small calls), and rows that start at any
+"""AFJL: the transpose's column and output kernels (D >= 1024: every number of destination rows, register and pass
+columns, one, a few and more than eight vectors); and forward calls whose fold items are split over several workgroups (small calls), and rows that start at any
 element (odd sizes in fp32 and bf16): against the fp64 oracle, one to 33 vectors, accumulated and in chunks of a
 small workspace."""
+import numpy as np
 import pytest
 import torch
 
 import oracle as O
-from test_gpu_parity import TOL_F32, dev, oracle_in, rand_inputs, rel_err  # noqa: F401
+from test_gpu_parity import TOL_BF16, TOL_F32, dev, oracle_in, rand_inputs, rel_err  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -32,4 +34,23 @@ def test_afjl_split_items(D, batch, ws_mb, dtype, dev, monkeypatch):  # noqa: F8
     y2 = s.apply(xd[:2])
     s.apply(xd[2:], out=y2, first_layer=2, accumulate=True)
     assert rel_err(y2.cpu().numpy(), ref) < TOL_F32
+    s.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("lgD,batch", [(10, 1), (10, 3), (11, 1), (12, 9), (13, 2), (14, 1), (15, 10), (16, 1), (16, 3),
+                                       (17, 1), (18, 2), (20, 1)])
+def test_afjl_transpose_rows(lgD, batch, dtype, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    D, seed = 1 << lgD, 40 + lgD
+    s = Sketch("afjl", LAYERS, D, seed, device=dev)
+    g = torch.Generator().manual_seed(seed)
+    z = torch.randn((batch, D), generator=g)
+    th = [torch.randn(r * c, generator=g) * 0.02 if i % 2 else None for i, (r, c) in enumerate(LAYERS)]
+    outs = s.apply_T(z.to(dev), out_dtype=torch.bfloat16 if dtype == "bf16" else torch.float32,
+                     theta0=[None if t is None else t.to(dev) for t in th])
+    refs = O.apply_T("afjl", LAYERS, D, seed, z.numpy().astype(np.float64),
+                     theta0=[None if t is None else t.numpy() for t in th])
+    for o, r in zip(outs, refs):
+        assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL_F32)
     s.close()
