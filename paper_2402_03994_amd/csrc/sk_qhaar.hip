@@ -45,6 +45,9 @@ namespace sk {
 namespace {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
+// rows of an input may start at any element: vector loads at the element's alignment
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(2)));
 
 // ---------------------------------------------------------------- factors
 // Householder QR of a (b x b, column-major, overwritten) and the explicit Q
@@ -124,7 +127,6 @@ struct QhArgs {
   int64_t p_off;  // kPStacked: first element of the rows (a slab's offset)
   int64_t o_off;  // kEBcast: first element written (a slab's offset)
   int nvec;       // slot form: vectors stacked
-  int q_vec;      // NN fold: 16-byte (fp32) / 8-byte (bf16) loads of the input allowed
   const void *q;  // Q: NT: fp32 N x K (ldq = K); NN buffer: fp32 K x N; NN fold: the input
   int64_t q_vs;
   int dtype;      // input dtype (kPInput, kQNNFold)
@@ -164,6 +166,16 @@ __device__ __forceinline__ float load_in(const void *x, int dtype, int64_t i) {
   return dtype == SK_BF16 ? bf16_to_f32(((const uint16_t *)x)[i]) : ((const float *)x)[i];
 }
 
+// Elements i .. i + 3 of the input.
+__device__ __forceinline__ f4v load_in4(const void *x, int dtype, int64_t i) {
+  if (dtype == SK_BF16) {
+    const u2u u = *(const u2u *)((const uint16_t *)x + i);
+    return f4v{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
+               __uint_as_float(u.y & 0xFFFF0000u)};
+  }
+  return *(const f4u *)((const float *)x + i);
+}
+
 // Four values of P at row `row`, columns k .. k + 3 (zero outside M x K or the input).
 template <int PM>
 __device__ __forceinline__ f4v load_p4(const QhArgs &a, int64_t v, int row, int k) {
@@ -177,12 +189,11 @@ __device__ __forceinline__ f4v load_p4(const QhArgs &a, int64_t v, int row, int 
       if (k + e < a.K) r[e] = p[k + e];
   } else {
     const int vv = row / a.p_rows, h = row - (row / a.p_rows) * a.p_rows;
-    const int64_t base = (a.b_in + vv) * a.n_in;
+    const int64_t base = (a.b_in + vv) * a.n_in, f = a.p_off + (int64_t)h * a.ldp + k;
+    if (k + 3 < a.K && f + 3 < a.n_in) return load_in4(a.p, a.dtype, base + f);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t f = a.p_off + (int64_t)h * a.ldp + k + e;
-      if (k + e < a.K && f < a.n_in) r[e] = load_in(a.p, a.dtype, base + f);
-    }
+    for (int e = 0; e < 4; ++e)
+      if (k + e < a.K && f + e < a.n_in) r[e] = load_in(a.p, a.dtype, base + f + e);
   }
   (void)v;
   return r;
@@ -196,26 +207,20 @@ __device__ __forceinline__ void load_tile(const QhArgs &a, int64_t v, int k0, in
   const int cc = c0 + 4 * (lane & 15);
   // a tile wholly inside K and the input (tested once, uniformly): every load
   // is issued without a branch, so they are all in flight together
-  if (QM == kQNNFold && a.q_vec && k0 + 15 < a.K &&
-      (int64_t)(PF - 1) * a.slab + (int64_t)(k0 + 15) * a.N + c0 + 63 < a.n_in) {
+  if (QM == kQNNFold && k0 + 15 < a.K && (int64_t)(PF - 1) * a.slab + (int64_t)(k0 + 15) * a.N + c0 + 63 < a.n_in) {
     const int64_t base = (a.b_in + v) * a.n_in;
     if (a.dtype == SK_BF16) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int t = 0; t < PF; ++t) {
-          const uint2 u = *(const uint2 *)((const uint16_t *)a.q + base + t * a.slab +
-                                           (int64_t)(k0 + 4 * q + (lane >> 4)) * a.N + cc);
-          r[t][q] = f4v{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
-                        __uint_as_float(u.y & 0xFFFF0000u)};
-        }
+        for (int t = 0; t < PF; ++t)
+          r[t][q] = load_in4(a.q, SK_BF16, base + t * a.slab + (int64_t)(k0 + 4 * q + (lane >> 4)) * a.N + cc);
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int t = 0; t < PF; ++t)
-          r[t][q] = *(const f4v *)((const float *)a.q + base + t * a.slab + (int64_t)(k0 + 4 * q + (lane >> 4)) * a.N +
-                                   cc);
+          r[t][q] = load_in4(a.q, SK_F32, base + t * a.slab + (int64_t)(k0 + 4 * q + (lane >> 4)) * a.N + cc);
     }
     return;
   }
@@ -234,14 +239,8 @@ __device__ __forceinline__ void load_tile(const QhArgs &a, int64_t v, int k0, in
 #pragma unroll
     for (int t = 0; t < PF; ++t) {
       const int64_t f = t * a.slab + (int64_t)k * a.N + cc;
-      if (a.q_vec && f + 3 < a.n_in) {
-        if (a.dtype == SK_BF16) {
-          const uint2 u = *(const uint2 *)((const uint16_t *)a.q + base + f);
-          r[t][q] = f4v{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
-                        __uint_as_float(u.y & 0xFFFF0000u)};
-        } else {
-          r[t][q] = *(const f4v *)((const float *)a.q + base + f);
-        }
+      if (f + 3 < a.n_in) {
+        r[t][q] = load_in4(a.q, a.dtype, base + f);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -253,16 +252,22 @@ __device__ __forceinline__ void load_tile(const QhArgs &a, int64_t v, int k0, in
 
 constexpr int kStageLd = 68;  // floats per staged row (64 + 4: 16-byte aligned rows)
 
-// One workgroup per (16 TA x 16 TB output block, vector); the four waves take
-// quarters of K and their partial blocks are added in wave order through LDS.
+// One workgroup per (16 TA x 16 TB output block, vector); the NW waves take
+// equal parts of K and their partial blocks are added in wave order through LDS.
 // Lane (li, g) of a 16 x 16 tile: P row li and Q column li, K slice 4 g .. 4 g
 // + 3 of each 16-wide step (one MFMA per slice element), output rows 4 g .. 4 g
 // + 3 of column li.  In the NN forms each wave stages its 16 x 64 tile of the
-// Q operand in its own part of the LDS block (loaded one step ahead, slabs
-// summed with their weights on the way in) and reads the MFMA fragments from
-// there.
-template <int TA, int TB, int PM, int QM, int PF, int EP, bool SL = false>
-__global__ __launch_bounds__(256) void k_qh_gemm(QhArgs a, QhSlots sl) {
+// Q operand in its own part of the LDS block (slabs summed with their weights
+// on the way in) and reads the MFMA fragments from there.  Both operands of the
+// next step are requested before the products of the present one.
+//
+// At 16 vectors and D = 2^16 a contraction has 256 blocks, one per CU, so what
+// is in flight is what its own waves request: four waves that requested a step
+// where they used it took 113 us for a fold of four slabs (268 MB, 57 us at the
+// copy rate) and 41 us for the second contraction (14 us of matrix
+// instructions); eight waves and a step ahead take 67 and 31 us.
+template <int NW, int TA, int TB, int PM, int QM, int PF, int EP, bool SL = false>
+__global__ __launch_bounds__(64 * NW) void k_qh_gemm(QhArgs a, QhSlots sl) {
   if (SL) {  // the slot's layer: Qt-first form, vectors' rows stacked
     const int z = blockIdx.z;
     a.p = sl.x[z];
@@ -276,14 +281,14 @@ __global__ __launch_bounds__(256) void k_qh_gemm(QhArgs a, QhSlots sl) {
   }
   constexpr int kRed = TA * TB * 256;
   constexpr int kWave = kRed > 16 * kStageLd ? kRed : 16 * kStageLd;
-  __shared__ __align__(16) float red[4][kWave];
+  __shared__ __align__(16) float red[NW][kWave];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, g = lane >> 4;
   const int nbb = a.N / (16 * TB);
   const int ba = blockIdx.x / nbb, bb = blockIdx.x - (blockIdx.x / nbb) * nbb;
   const int64_t v = blockIdx.y;
   const int r0 = ba * TA * 16, c0 = bb * TB * 16;
-  const int per = ((a.K + 63) / 64) * 16;
+  const int per = ((a.K + 16 * NW - 1) / (16 * NW)) * 16;
   const int kb = wave * per, ke = kb + per < a.K ? kb + per : a.K;
   float *stage = red[wave];
   f4v acc[TA][TB];
@@ -292,24 +297,35 @@ __global__ __launch_bounds__(256) void k_qh_gemm(QhArgs a, QhSlots sl) {
 #pragma unroll
     for (int j = 0; j < TB; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
   constexpr int NR = QM == kQNT ? 1 : PF;
-  f4v raw[NR][4];
-  if (QM != kQNT && kb < ke) load_tile<QM, NR>(a, v, kb, c0, lane, raw);
-  for (int k0 = kb; k0 < ke; k0 += 16) {
-    f4v pv[TA], qv[TB];
+  f4v raw[NR][4], pn[TA], qn[TB];
+  auto request = [&](int k0) {
     if (PM == kPBuf && a.p_vec && r0 + 16 * TA <= a.M && k0 + 15 < a.K) {
       // the workgroup's rows and this step wholly inside P (tested once): no per-load branch
       const float *pb = (const float *)a.p + v * a.p_vs;
 #pragma unroll
-      for (int i = 0; i < TA; ++i) pv[i] = *(const f4v *)(pb + (int64_t)(r0 + 16 * i + li) * a.ldp + k0 + 4 * g);
+      for (int i = 0; i < TA; ++i) pn[i] = *(const f4v *)(pb + (int64_t)(r0 + 16 * i + li) * a.ldp + k0 + 4 * g);
     } else {
 #pragma unroll
-      for (int i = 0; i < TA; ++i) pv[i] = load_p4<PM>(a, v, r0 + 16 * i + li, k0 + 4 * g);
+      for (int i = 0; i < TA; ++i) pn[i] = load_p4<PM>(a, v, r0 + 16 * i + li, k0 + 4 * g);
     }
     if (QM == kQNT) {
       // Q rows are output columns, K-contiguous; K is a multiple of 16 here
 #pragma unroll
       for (int j = 0; j < TB; ++j)
-        qv[j] = *(const f4v *)((const float *)a.q + v * a.q_vs + (int64_t)(c0 + 16 * j + li) * a.K + k0 + 4 * g);
+        qn[j] = *(const f4v *)((const float *)a.q + v * a.q_vs + (int64_t)(c0 + 16 * j + li) * a.K + k0 + 4 * g);
+    } else {
+      load_tile<QM, NR>(a, v, k0, c0, lane, raw);
+    }
+  };
+  if (kb < ke) request(kb);
+  for (int k0 = kb; k0 < ke; k0 += 16) {
+    f4v pv[TA], qv[TB];
+#pragma unroll
+    for (int i = 0; i < TA; ++i) pv[i] = pn[i];
+    if (QM == kQNT) {
+#pragma unroll
+      for (int j = 0; j < TB; ++j) qv[j] = qn[j];
+      if (k0 + 16 < ke) request(k0 + 16);
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -321,7 +337,7 @@ __global__ __launch_bounds__(256) void k_qh_gemm(QhArgs a, QhSlots sl) {
         }
         *(f4v *)(stage + (4 * q + (lane >> 4)) * kStageLd + 4 * (lane & 15)) = x;
       }
-      if (k0 + 16 < ke) load_tile<QM, NR>(a, v, k0 + 16, c0, lane, raw);
+      if (k0 + 16 < ke) request(k0 + 16);
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int j = 0; j < TB; ++j)
@@ -339,20 +355,20 @@ __global__ __launch_bounds__(256) void k_qh_gemm(QhArgs a, QhSlots sl) {
 #pragma unroll
   for (int i = 0; i < TA; ++i)
 #pragma unroll
-    for (int j = 0; j < TB; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) red[wave][((i * TB + j) * 64 + lane) * 4 + q] = acc[i][j][q];
+    for (int j = 0; j < TB; ++j) *(f4v *)&red[wave][((i * TB + j) * 64 + lane) * 4] = acc[i][j];
   __syncthreads();
-  for (int e = threadIdx.x; e < TA * TB * 64; e += 256) {
+  for (int e = threadIdx.x; e < TA * TB * 64; e += 64 * NW) {
     const int tile = e >> 6, ln = e & 63;
     const int i = tile / TB, j = tile - (tile / TB) * TB;
     const int col = c0 + 16 * j + (ln & 15);
+    f4v yq = *(const f4v *)&red[0][e * 4];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) yq += *(const f4v *)&red[w][e * 4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int row = r0 + 16 * i + (ln >> 4) * 4 + q;
       if (row >= a.M) continue;
-      const int o = (tile * 64 + ln) * 4 + q;
-      const float y = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
+      const float y = yq[q];
       if (EP == kEStore) {
         ((float *)a.dst)[v * a.c_vs + (int64_t)row * a.ldc + col] = y;
       } else if (EP == kEOut) {
@@ -379,10 +395,9 @@ __global__ __launch_bounds__(256) void k_qh_gemm(QhArgs a, QhSlots sl) {
 }
 
 // X'[v] (K x N) = sum_t w[t] X_t of the input (P slabs of K N elements), fp32.
-// The slabs are read with 16-byte (fp32) or 8-byte (bf16) loads when vec is
-// set, four slabs in flight per step.
+// Four slabs in flight per step.
 __global__ __launch_bounds__(256) void k_qh_fold(const void *x, int dtype, int64_t n_in, int64_t b_in,
-                                                 const float *__restrict__ w, int nslab, int64_t slab, int vec,
+                                                 const float *__restrict__ w, int nslab, int64_t slab,
                                                  float *__restrict__ dst) {
   const int64_t e = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * 4;
   const int64_t v = blockIdx.y;
@@ -397,14 +412,8 @@ __global__ __launch_bounds__(256) void k_qh_fold(const void *x, int dtype, int64
       const int64_t f = t * slab + e;
       r[u] = f4v{0.f, 0.f, 0.f, 0.f};
       if (t >= nslab) continue;
-      if (vec && f + 3 < n_in) {
-        if (dtype == SK_BF16) {
-          const uint2 q = *(const uint2 *)((const uint16_t *)x + base + f);
-          r[u] = f4v{__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xFFFF0000u), __uint_as_float(q.y << 16),
-                     __uint_as_float(q.y & 0xFFFF0000u)};
-        } else {
-          r[u] = *(const f4v *)((const float *)x + base + f);
-        }
+      if (f + 3 < n_in) {
+        r[u] = load_in4(x, dtype, base + f);
       } else {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -473,19 +482,36 @@ __global__ __launch_bounds__(256) void k_qh_mtab(const float *__restrict__ c, in
 
 int tiles_for(int m) { return m >= 64 ? 4 : m > 16 ? 2 : 1; }
 
+// Waves per workgroup: eight where each still has two steps of 16 or more (K
+// >= 256), else four.  A 600-wide block's weights: one vector 218 -> 136 us at
+// D = 2^14 and 327 -> 237 us at 2^17; 16 vectors at 2^17 (more blocks than CUs
+// already) 520 -> 504 us.
+int waves_for(int k) { return k >= 256 ? 8 : 4; }
+
+template <int PM, int QM, int PF, int EP, bool SL>
+void launch_tiles(const QhArgs &a, const QhSlots &sl, int mmax, unsigned gy, unsigned gz, hipStream_t st) {
+  const int ta = tiles_for(mmax);
+  constexpr int TB = 4;  // N = 1024
+  const unsigned nba = (unsigned)((mmax + 16 * ta - 1) / (16 * ta));
+  const dim3 grid(nba * (unsigned)(a.N / (16 * TB)), gy, gz);
+  auto go = [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    if (ta == 4)
+      hipLaunchKernelGGL((k_qh_gemm<NW, 4, TB, PM, QM, PF, EP, SL>), grid, dim3(64 * NW), 0, st, a, sl);
+    else if (ta == 2)
+      hipLaunchKernelGGL((k_qh_gemm<NW, 2, TB, PM, QM, PF, EP, SL>), grid, dim3(64 * NW), 0, st, a, sl);
+    else
+      hipLaunchKernelGGL((k_qh_gemm<NW, 1, TB, PM, QM, PF, EP, SL>), grid, dim3(64 * NW), 0, st, a, sl);
+  };
+  if (QM == kQNT || waves_for(a.K) == 8)  // K = 1024 in the NT forms
+    go(std::integral_constant<int, 8>{});
+  else if constexpr (QM != kQNT)
+    go(std::integral_constant<int, 4>{});
+}
+
 template <int PM, int QM, int PF, int EP>
 void launch_gemm(const QhArgs &a, int64_t bc, hipStream_t st) {
-  const int ta = tiles_for(a.M);
-  constexpr int TB = 4;  // N = 1024
-  const unsigned nba = (unsigned)((a.M + 16 * ta - 1) / (16 * ta));
-  const dim3 grid(nba * (unsigned)(a.N / (16 * TB)), (unsigned)bc);
-  const QhSlots none{};
-  if (ta == 4)
-    hipLaunchKernelGGL((k_qh_gemm<4, TB, PM, QM, PF, EP>), grid, dim3(256), 0, st, a, none);
-  else if (ta == 2)
-    hipLaunchKernelGGL((k_qh_gemm<2, TB, PM, QM, PF, EP>), grid, dim3(256), 0, st, a, none);
-  else
-    hipLaunchKernelGGL((k_qh_gemm<1, TB, PM, QM, PF, EP>), grid, dim3(256), 0, st, a, none);
+  launch_tiles<PM, QM, PF, EP, false>(a, QhSlots{}, a.M, (unsigned)bc, 1u, st);
 }
 
 // out[v][idx] (+)= sum over the slots in order of g . (A[:, :r] U): one thread per (column, vector, row).
@@ -752,15 +778,7 @@ void run_qh_small_group(const sk_sketch *s, int l0, int l1, int gi, const void *
     a.dst = ws;
     a.ldc = T;
     const int mmax = (int)(bc * maxr);
-    const int ta = tiles_for(mmax);
-    const unsigned nba = (unsigned)((mmax + 16 * ta - 1) / (16 * ta));
-    const dim3 grid(nba * (unsigned)(T / 64), 1u, (unsigned)sl.n);
-    if (ta == 4)
-      hipLaunchKernelGGL((k_qh_gemm<4, 4, kPStacked, kQNT, 1, kEStore, true>), grid, dim3(256), 0, st, a, sl);
-    else if (ta == 2)
-      hipLaunchKernelGGL((k_qh_gemm<2, 4, kPStacked, kQNT, 1, kEStore, true>), grid, dim3(256), 0, st, a, sl);
-    else
-      hipLaunchKernelGGL((k_qh_gemm<1, 4, kPStacked, kQNT, 1, kEStore, true>), grid, dim3(256), 0, st, a, sl);
+    launch_tiles<kPStacked, kQNT, 1, kEStore, true>(a, sl, mmax, 1u, (unsigned)sl.n, st);
   }
   if (phases & 2) {
     const dim3 grid(T / 256, (unsigned)bc, (unsigned)dm);
@@ -799,7 +817,6 @@ void run_qh_apply(const sk_sketch *s, int layer, const void *x, int dtype, int64
     a.c_vs = (int64_t)ld.qdm * T;
     a.ldc = T;
     a.q = x;
-    a.q_vec = ld.n % 4 == 0 && ((uintptr_t)x & (dtype == SK_BF16 ? 7 : 15)) == 0;
     a.w = w;
     a.nslab = (int)ld.qP;
     a.slab = (int64_t)ld.qbm * T;
@@ -811,8 +828,7 @@ void run_qh_apply(const sk_sketch *s, int layer, const void *x, int dtype, int64
       launch_gemm<kPBuf, kQNNFold, 4, kEStore>(a, bc, st);
     } else {
       const dim3 fg((unsigned)((a.slab / 4 + 255) / 256), (unsigned)bc);
-      hipLaunchKernelGGL(k_qh_fold, fg, dim3(256), 0, st, x, dtype, ld.n, b_begin, w, (int)ld.qP, a.slab, a.q_vec,
-                         xf);
+      hipLaunchKernelGGL(k_qh_fold, fg, dim3(256), 0, st, x, dtype, ld.n, b_begin, w, (int)ld.qP, a.slab, xf);
       a.q = xf;
       a.q_vs = a.slab;
       launch_gemm<kPBuf, kQNNBuf, 1, kEStore>(a, bc, st);
