@@ -74,9 +74,10 @@ void free_all(sk_sketch *s) {
   f(s->d_fjl_lsmp);
   f(s->d_fjl_lpos);
   f(s->d_fjl_loff);
-  f(s->d_fjlb_off);
-  f(s->d_fjlb_ent);
   f(s->d_fjlb_pos);
+  f(s->d_fjlb_ent);
+  f(s->d_fjlb_id);
+  f(s->d_fjlb_off);
   f(s->d_qka);
   f(s->d_qkb);
   f(s->d_qkah);
@@ -414,11 +415,11 @@ int sketch_create(sk_kind kind, const sk_layer_shape *shapes, int32_t n_layers, 
   }
 
   // FJL transpose: samples grouped by position (deterministic order).
-  std::vector<uint32_t> fpos, fseg, fsmp, ftoff, flsmp, flpos, floff, fboff, fbent, fbpos;
+  std::vector<uint32_t> fpos, fseg, fsmp, ftoff, flsmp, flpos, floff, fbpos, fbent, fboff;
+  std::vector<uint16_t> fbid;
   if (kind == SK_FJL) {
     s->fjlb_pos_at.assign(n_layers, -1);
     s->fjlb_off_at.assign(n_layers, -1);
-    s->fjlb_ent_at.assign(n_layers, -1);
     s->fjl_uoff.assign(n_layers + 1, 0);
     s->fjl_toff_at.assign(n_layers, 0);
     s->fjl_loff_at.assign(n_layers, 0);
@@ -473,27 +474,28 @@ int sketch_create(sk_kind kind, const sk_layer_shape *shapes, int32_t n_layers, 
           flpos[(size_t)l * D + i] = sample_index((uint64_t)bs[i].second, (uint32_t)l, s->key, (uint64_t)ld.np);
         }
       }
-      if (fjl_onepass_T_ok(ld.lgnp, D)) {
-        // cell (p_h, p_c) = (p >> 13, low B = 26 - lgnp bits) of the one-pass transpose's tile; entries of a
-        // cell by id, each (id << 8) | the H = lgnp - 13 middle bits
+      if (fjl_onepass_ok(ld.lgnp, D)) {
+        // a sample's word: cell (p >> 13, low B = 26 - lgnp bits) of the one-pass tile and the H = lgnp - 13
+        // middle bits; by id, and by (rank among the cell's samples, id) with the ranks' first entries
         const int Hb = ld.lgnp - 13, Bb = 13 - Hb;
-        std::vector<std::pair<uint32_t, uint32_t>> cs(D);
+        std::vector<uint16_t> seen(1 << 13, 0);
+        std::vector<std::pair<uint32_t, uint32_t>> ri(D);  // (rank, id)
+        s->fjlb_pos_at[l] = (int64_t)fbpos.size();
         for (int64_t i = 0; i < D; ++i) {
           const uint32_t p = sample_index((uint64_t)i, (uint32_t)l, s->key, (uint64_t)ld.np);
           const uint32_t cell = ((p >> 13) << Bb) | (p & ((1u << Bb) - 1));
-          cs[i] = {cell, ((uint32_t)i << 8) | ((p >> Bb) & ((1u << Hb) - 1))};
+          ri[i] = {seen[cell]++, (uint32_t)i};
+          fbpos.push_back((cell << 8) | ((p >> Bb) & ((1u << Hb) - 1)));
         }
-        s->fjlb_pos_at[l] = (int64_t)fbpos.size();
-        for (int64_t i = 0; i < D; ++i) fbpos.push_back((cs[i].first << 8) | (cs[i].second & 255u));
-        std::sort(cs.begin(), cs.end());
+        std::sort(ri.begin(), ri.end());
         s->fjlb_off_at[l] = (int64_t)fboff.size();
-        s->fjlb_ent_at[l] = (int64_t)fbent.size();
-        int64_t k = 0;
-        for (uint32_t c = 0; c <= 8192; ++c) {
-          while (k < D && cs[k].first < c) ++k;
-          fboff.push_back((uint32_t)k);
+        const uint32_t *word = fbpos.data() + s->fjlb_pos_at[l];
+        for (int64_t i = 0; i < D; ++i) {
+          if (i == 0 || ri[i].first != ri[i - 1].first) fboff.push_back((uint32_t)i);
+          fbent.push_back(word[ri[i].second]);
+          fbid.push_back((uint16_t)ri[i].second);
         }
-        for (int64_t i = 0; i < D; ++i) fbent.push_back(cs[i].second);
+        fboff.push_back((uint32_t)D);
       }
     }
   }
@@ -558,10 +560,11 @@ int sketch_create(sk_kind kind, const sk_layer_shape *shapes, int32_t n_layers, 
   SK_TRY(alloc((void **)&s->d_fjl_lsmp, sizeof(uint32_t) * flsmp.size()));
   SK_TRY(alloc((void **)&s->d_fjl_lpos, sizeof(uint32_t) * flpos.size()));
   SK_TRY(alloc((void **)&s->d_fjl_loff, sizeof(uint32_t) * floff.size()));
-  if (!fboff.empty()) {
-    SK_TRY(alloc((void **)&s->d_fjlb_off, sizeof(uint32_t) * fboff.size()));
-    SK_TRY(alloc((void **)&s->d_fjlb_ent, sizeof(uint32_t) * fbent.size()));
+  if (!fbpos.empty()) {
     SK_TRY(alloc((void **)&s->d_fjlb_pos, sizeof(uint32_t) * fbpos.size()));
+    SK_TRY(alloc((void **)&s->d_fjlb_ent, sizeof(uint32_t) * fbent.size()));
+    SK_TRY(alloc((void **)&s->d_fjlb_id, sizeof(uint16_t) * fbid.size()));
+    SK_TRY(alloc((void **)&s->d_fjlb_off, sizeof(uint32_t) * fboff.size()));
   }
   SK_TRY(alloc((void **)&s->d_qka, sizeof(float) * fac_a));
   SK_TRY(alloc((void **)&s->d_qkb, sizeof(uint16_t) * 2 * fac_b));
@@ -586,10 +589,11 @@ int sketch_create(sk_kind kind, const sk_layer_shape *shapes, int32_t n_layers, 
   SK_TRY(h2d(s->d_fjl_lsmp, flsmp.data(), sizeof(uint32_t) * flsmp.size()));
   SK_TRY(h2d(s->d_fjl_lpos, flpos.data(), sizeof(uint32_t) * flpos.size()));
   SK_TRY(h2d(s->d_fjl_loff, floff.data(), sizeof(uint32_t) * floff.size()));
-  if (!fboff.empty()) {
-    SK_TRY(h2d(s->d_fjlb_off, fboff.data(), sizeof(uint32_t) * fboff.size()));
-    SK_TRY(h2d(s->d_fjlb_ent, fbent.data(), sizeof(uint32_t) * fbent.size()));
+  if (!fbpos.empty()) {
     SK_TRY(h2d(s->d_fjlb_pos, fbpos.data(), sizeof(uint32_t) * fbpos.size()));
+    SK_TRY(h2d(s->d_fjlb_ent, fbent.data(), sizeof(uint32_t) * fbent.size()));
+    SK_TRY(h2d(s->d_fjlb_id, fbid.data(), sizeof(uint16_t) * fbid.size()));
+    SK_TRY(h2d(s->d_fjlb_off, fboff.data(), sizeof(uint32_t) * fboff.size()));
   }
 
   // workspace: room for up to 256 vectors of the largest per-vector need
@@ -1178,7 +1182,7 @@ int sketch_apply_T(sk_sketch *s, const float *z, int64_t batch, void *const *out
           SK_PROF(SK_PROF_GATHER, obytes, launch_affd_T_out(s, l, s->ws, b0, bc, o, out_dtype, th, st));
           break;
         case SK_FJL: {
-          if (s->fjlb_off_at[l] >= 0) {
+          if (s->fjlb_pos_at[l] >= 0) {
             SK_PROF(SK_PROF_FJL_T, obytes + bc * s->D * 4,
                     launch_fjl_T_onepass(s, l, z, b0, bc, o, out_dtype, th, st));
             break;

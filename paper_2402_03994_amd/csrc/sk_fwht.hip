@@ -1529,169 +1529,248 @@ void launch_fjl_last_signed(const sk_sketch *s, int layer, const float *w, int l
   SK_CHECK_LAUNCH();
 }
 
-// FJL transpose in one pass, 2^14 <= N' <= 2^21, D <= 2^13 (the adjoint of
-// eq. ailon_chazelle).  With N' = 2^(13 + H) a coordinate is j = (h, a, c): h
-// the top H bits, a the next H, c the low B = 13 - H (>= 5); the normalised
-// transform factors as H_N'[j, p] = H[h, p_h] H[a, p_a] H[c, p_c] / sqrt(N').
-// Workgroup (a, vector): the 2^H x 2^B tile U[p_h][p_c] = sum over samples i
-// at (p_h, p_a, p_c) of H[a, p_a] g_i z_i, its unnormalised 13-bit transform,
-// then signs, the scale 1/sqrt(D) and theta0; every output is written once.
-// The products H[a, p_a] g_i z_i are made first, all loads of a thread in
-// flight together, and staged in LDS in cell order; each cell is then summed
-// by one thread in id order (deterministic), the cell offsets loaded in one
-// batch.
-bool fjl_onepass_T_ok(int lgnp, int64_t D) { return lgnp >= 14 && lgnp <= 21 && D <= (1 << 13); }
+// FJL in one pass, 2^14 <= N' <= 2^21, D <= 2^13 (eq. ailon_chazelle and its
+// adjoint).  With N' = 2^(13 + H) a coordinate is j = (h, a, c): h the top H
+// bits, a the next H, c the low B = 13 - H (>= 5); the normalised transform
+// factors as H_N'[j, p] = H[h, p_h] H[a, p_a] H[c, p_c] / sqrt(N').  A
+// workgroup holds a 2^H x 2^B tile, cell k = (h, c), of one a and one vector;
+// a sample's table word is its cell (from bit 8) and p_a (bits 0-7).  The
+// forward has the words by id, the transpose by (rank, id), the rank of a
+// sample being the number of earlier ids in its cell, with the ids and the
+// ranks' first entries.
+bool fjl_onepass_ok(int lgnp, int64_t D) { return lgnp >= 14 && lgnp <= 21 && D <= (1 << 13); }
 
-template <int R>  // entries per thread: D <= 256 R
-__global__ __launch_bounds__(256) void k_fjl_T_onepass(const LayerDesc *__restrict__ layers, int layer,
-                                                       const float *__restrict__ gtab,
-                                                       const uint32_t *__restrict__ boff,
-                                                       const uint32_t *__restrict__ bent,
-                                                       const float *__restrict__ z, int D, int64_t b_begin,
-                                                       void *__restrict__ out, int out_dtype,
-                                                       const float *__restrict__ theta0, float scale, Key key) {
-  extern __shared__ float sm[];
-  float *tile = sm;                                                        // p16 layout, 2^13 cells
-  float *ce = sm;                                                          // first: the D products, cell order
-  uint32_t *sw = reinterpret_cast<uint32_t *>(sm + p16_floats(1 << 13));  // sign words in tile order
+// Tile cell k in LDS: four words after every 256 keep both layouts below on 32
+// distinct banks per half-wave.
+constexpr int kFjlTile = 8192 + 32 * 4;
+__device__ __forceinline__ int fjl_at(int k) { return k + ((k >> 8) << 2); }
+
+template <int CTRL>
+__device__ __forceinline__ float fjl_quad(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+// The 13-bit transform takes two register passes.  Layout A: thread t holds
+// cells t + 256 m (m < 32), bits 8-12 in registers.  Layout B: bits 3-7 in
+// registers, bits 0-1 in lane bits 0-1 (exchanged inside quads), bit 2 in lane
+// bit 5 (exchanged with register bit 0 by half-wave swaps), bits 8-10 in lane
+// bits 2-4 and bits 11-12 the wave.
+__device__ __forceinline__ int fjl_b_cell() {  // the thread's cell of register 0
+  const int l = threadIdx.x & 63;
+  return (l & 3) | ((l >> 5) << 2) | (((l >> 2) & 7) << 8) | ((int)(threadIdx.x >> 6) << 11);
+}
+
+// Layout B: transforms bits 0-7 of the tile (each wave reads and writes its own
+// quarter of the tile only; the caller synchronises).
+__device__ __forceinline__ void fjl_low_bits(float *tile) {
+  const int l = threadIdx.x & 63;
+  const float s0 = l & 1 ? -1.0f : 1.0f, s1 = l & 2 ? -1.0f : 1.0f;
+  const int base = fjl_at(fjl_b_cell());
+  float e[32];
+#pragma unroll
+  for (int r = 0; r < 32; ++r) e[r] = tile[base + 8 * r];
+  fwht_regs_t<32>(e);
+#pragma unroll
+  for (int r = 0; r < 32; ++r) e[r] = fmaf(e[r], s0, fjl_quad<0xB1>(e[r]));
+#pragma unroll
+  for (int r = 0; r < 32; ++r) e[r] = fmaf(e[r], s1, fjl_quad<0x4E>(e[r]));
+  // lane bit 5 <-> register bit 0; then cell bit 2 is register bit 0 and bit 3 lane bit 5
+#pragma unroll
+  for (int r = 0; r < 32; r += 2) {
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(e[r]), __float_as_uint(e[r + 1]), false, false);
+    const float x = __uint_as_float(q[0]), y = __uint_as_float(q[1]);
+    e[r] = x + y;
+    e[r + 1] = x - y;
+  }
+  const int wb = base + ((l >> 5) << 2);  // cell bit 3 from lane bit 5 in place of bit 2
+#pragma unroll
+  for (int r = 0; r < 32; r += 2) {
+    tile[wb + 8 * r] = e[r];
+    tile[wb + 8 * r + 4] = e[r + 1];
+  }
+}
+
+// The signs of the thread's cells in layout A: lane l computes the word of the
+// 32 cells of half l & 1 of m = l >> 1, and the two words of an m are that m's
+// lane mask.
+__device__ __forceinline__ uint32_t fjl_sign_word(int a, int B, uint32_t layer_id, Key key) {
+  const int l = threadIdx.x & 63;
+  const int w = 2 * (int)(threadIdx.x >> 6) + (l & 1) + 8 * (l >> 1);  // cells 32 w .. 32 w + 31
+  const int64_t j = ((int64_t)(w >> (B - 5)) << 13) + ((int64_t)a << B) + ((w & ((1 << (B - 5)) - 1)) << 5);
+  return sign_word((uint64_t)j, layer_id, key);
+}
+__device__ __forceinline__ float fjl_signed(float v, uint32_t word, int m) {
+  const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(word, 2 * m) |
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(word, 2 * m + 1) << 32);
+  return __builtin_amdgcn_inverse_ballot_w64(mask) ? -v : v;
+}
+
+// Coordinate offset of cell k without its a part.
+__device__ __forceinline__ uint32_t fjl_coord(int k, int B) {
+  return ((uint32_t)(k >> B) << 13) + (uint32_t)(k & ((1 << B) - 1));
+}
+
+// Transpose.  U[p_h][p_c] = sum over the samples i at (p_h, p_a, p_c) of
+// H[a, p_a] g_i z_i; its transform, signs, the scale 1/sqrt(D) and theta0 are
+// the outputs of the workgroup's a, each written once.  The samples of rank 0
+// are stored into the zeroed tile, those of rank 1, 2, ... are added with a
+// barrier between ranks: every cell is the sum in id order (deterministic) and
+// a register of 256 samples is visited once per rank it holds.
+// Bound by latency and LDS (4 workgroups per CU): N' = 2^20, D = 2^12, 8
+// vectors 38.7 us with the cells' lists walked, theta0 read per output and four LDS
+// passes, 19.4 us so.
+template <int R>  // samples per thread: D <= 256 R
+__global__ __launch_bounds__(256, R <= 16 ? 4 : 3) void k_fjl_T_onepass(const LayerDesc *__restrict__ layers, int layer,
+                                                          const float *__restrict__ gtab,
+                                                          const uint32_t *__restrict__ bent,
+                                                          const uint16_t *__restrict__ bid,
+                                                          const uint32_t *__restrict__ boff,
+                                                          const float *__restrict__ z, int D, int64_t b_begin,
+                                                          void *__restrict__ out, int out_dtype,
+                                                          const float *__restrict__ theta0, float scale, Key key) {
+  __shared__ float tile[kFjlTile];
   const LayerDesc &ld = layers[layer];
-  const int H = ld.lgnp - 13, B = 13 - H;
-  const int a = blockIdx.x;
+  const int B = 26 - ld.lgnp;
+  const int a = blockIdx.x, tid = threadIdx.x;
   const int64_t v = blockIdx.y;
   const float *g = gtab + (int64_t)layer * D;
   const float *zv = z + (b_begin + v) * D;
-  // cell offsets of the thread's 32 cells k = tid + 256 m, both ends
-  uint32_t o0[32], o1[32];
+  uint32_t q[R];
+  uint16_t id[R];
+  float gz[R], zr[R];
 #pragma unroll
-  for (int m = 0; m < 32; ++m) {
-    o0[m] = boff[threadIdx.x + 256 * m];
-    o1[m] = boff[threadIdx.x + 256 * m + 1];
+  for (int r = 0; r < R; ++r) {
+    const int i = tid + 256 * r, ic = i < D ? i : D - 1;
+    q[r] = bent[ic];
+    id[r] = bid[ic];
   }
-  // products of entries e = tid + 256 r (r < R)
-  {
-    uint32_t q[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = threadIdx.x + 256 * r;
-      q[r] = e < D ? bent[e] : 0u;
-    }
-    float gz[R];
-    if (R <= 16) {
-      // D <= 4096: g z by id, loaded in order, staged after the products (inside the tile), then
-      // gathered from LDS in cell order
-      float *gzs = sm + D;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int i = threadIdx.x + 256 * r;
-        if (i < D) gzs[i] = g[i] * zv[i];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = threadIdx.x + 256 * r;
-        gz[r] = e < D ? gzs[q[r] >> 8] : 0.0f;
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = threadIdx.x + 256 * r;
-        const uint32_t i = q[r] >> 8;
-        gz[r] = e < D ? g[i] * zv[i] : 0.0f;
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = threadIdx.x + 256 * r;
-      if (e < D) ce[e] = flip(gz[r], (uint32_t)__popc((uint32_t)a & q[r] & 255u) & 1u);
-    }
+  for (int r = 0; r < R; ++r) {
+    gz[r] = g[id[r]];
+    zr[r] = zv[id[r]];
   }
-  {
-    // word w: tile cells 32 w .. 32 w + 31 = row h = w >> (B - 5), columns from 32 (w mod 2^(B - 5))
-    const int w = threadIdx.x;
-    const int64_t j = ((int64_t)(w >> (B - 5)) << 13) + ((int64_t)a << B) + ((w & ((1 << (B - 5)) - 1)) << 5);
-    sw[w] = sign_word((uint64_t)j, (uint32_t)ld.layer_id, key);
+#pragma unroll
+  for (int m = 0; m < 32; ++m) tile[tid + 260 * m] = 0.0f;
+  const uint32_t word = fjl_sign_word(a, B, (uint32_t)ld.layer_id, key);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    gz[r] = flip(gz[r] * zr[r], (uint32_t)__popc((uint32_t)a & q[r] & 255u) & 1u);
   }
   __syncthreads();
-  float u[32];
+  uint32_t beg = 0, end = boff[1];  // the samples of the rank
+  int rank = 0;
 #pragma unroll
-  for (int m = 0; m < 32; ++m) {
-    float acc = 0.0f;
-    for (uint32_t e = o0[m]; e < o1[m]; ++e) acc += ce[e];
-    u[m] = acc;
+  for (int r = 0; r < R; ++r) {
+    const uint32_t lo = 256u * r, hi = lo + 256u < (uint32_t)D ? lo + 256u : (uint32_t)D, e = lo + tid;
+    if (lo >= (uint32_t)D) break;
+    for (;;) {  // the ranks of this register's samples (uniform)
+      if (e >= beg && e < end) {
+        float *c = tile + fjl_at((int)(q[r] >> 8));
+        *c = rank == 0 ? gz[r] : *c + gz[r];
+      }
+      if (end > hi || end == (uint32_t)D) break;
+      beg = end;
+      end = boff[++rank + 1];
+      __syncthreads();
+      if (beg == hi) break;  // the next register opens the rank
+    }
   }
-  __syncthreads();  // the products are read; the tile takes their place
+  const uint32_t jt = fjl_coord(tid, B) + ((uint32_t)a << B), nlast = (uint32_t)(ld.n - 1);
+  float th[32];
+  if (theta0) {  // in flight during the transform
 #pragma unroll
-  for (int m = 0; m < 32; ++m) tile[p16(threadIdx.x + 256 * m)] = u[m];
-  lds_fwht_regs(tile, 13, 0);  // opens and closes with a barrier
+    for (int m = 0; m < 32; ++m) {
+      const uint32_t j = jt + fjl_coord(256 * m, B);
+      th[m] = theta0[j < nlast ? j : nlast];
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < 32; ++m) th[m] = -0.0f;  // x + -0 = x for every x
+  }
+  __syncthreads();
+  fjl_low_bits(tile);
+  __syncthreads();
+  float e[32];
+#pragma unroll
+  for (int m = 0; m < 32; ++m) e[m] = tile[tid + 260 * m];
+  fwht_regs_t<32>(e);
+#pragma unroll
+  for (int m = 0; m < 32; ++m) e[m] = fjl_signed(e[m] * scale, word, m) + th[m];
   const int64_t row = (b_begin + v) * ld.n;
-  for (int m = 0; m < 32; ++m) {
-    const int k = threadIdx.x + 256 * m;
-    const int64_t j = ((int64_t)(k >> B) << 13) + ((int64_t)a << B) + (k & ((1 << B) - 1));
-    if (j < ld.n) {
-      float val = flip(tile[p16(k)] * scale, (sw[k >> 5] >> (k & 31)) & 1u);
-      if (theta0) val += theta0[j];
-      store_out(out, out_dtype, row + j, val);
+  if (out_dtype == SK_BF16) {
+    uint16_t *oh = (uint16_t *)out + row;
+#pragma unroll
+    for (int m = 0; m < 32; ++m) {
+      const uint32_t j = jt + fjl_coord(256 * m, B);
+      if (j <= nlast) oh[j] = f32_to_bf16(e[m]);
+    }
+  } else {
+    float *of = (float *)out + row;
+#pragma unroll
+    for (int m = 0; m < 32; ++m) {
+      const uint32_t j = jt + fjl_coord(256 * m, B);
+      if (j <= nlast) of[j] = e[m];
     }
   }
 }
 
-// FJL forward in one pass for the same layers (eq. ailon_chazelle), the
-// factorisation above read the other way: workgroup (a, vector) loads the
-// tile X[h][c] = b_j x_j of the coordinates j = (h, a, c) (runs of 2^B >= 32
-// consecutive ones), transforms it (Y = (H (x) H) X over all 13 bits), and
-// writes for every sample i at p = (p_h, p_a, p_c) its share
-// H[a, p_a] Y[p_h][p_c] g_i / sqrt(D) into partial slot a; the 2^H slots are
-// then summed in a fixed order (launch_reduce_partials).
+// Forward.  The tile X[h][c] = b_j x_j of the workgroup's a (runs of 2^B >= 32
+// consecutive coordinates), transformed; sample i gets the share H[a, p_a]
+// Y[p_h][p_c] g_i / sqrt(D) in partial slot a, and the 2^H slots are summed in
+// a fixed order (launch_reduce_partials).  N' = 2^20, D = 2^12, 8 vectors:
+// 22.4 us with four LDS passes, 14.4 us with two register passes.
 template <bool BF16, int R>
-__global__ __launch_bounds__(256) void k_fjl_fwd_onepass(const LayerDesc *__restrict__ layers, int layer,
-                                                         const float *__restrict__ gtab,
-                                                         const uint32_t *__restrict__ bpos,
-                                                         const void *__restrict__ x, int D, int64_t b_begin,
-                                                         int64_t bc, float *__restrict__ part, float scale, Key key) {
-  extern __shared__ float sm[];
-  float *tile = sm;                                                        // p16 layout, 2^13 cells
-  uint32_t *sw = reinterpret_cast<uint32_t *>(sm + p16_floats(1 << 13));  // sign words in tile order
+__global__ __launch_bounds__(256, 4) void k_fjl_fwd_onepass(const LayerDesc *__restrict__ layers, int layer,
+                                                            const float *__restrict__ gtab,
+                                                            const uint32_t *__restrict__ bpos,
+                                                            const void *__restrict__ x, int D, int64_t b_begin,
+                                                            int64_t bc, float *__restrict__ part, float scale,
+                                                            Key key) {
+  __shared__ float tile[kFjlTile];
   const LayerDesc &ld = layers[layer];
-  const int H = ld.lgnp - 13, B = 13 - H;
-  const int a = blockIdx.x;
+  const int B = 26 - ld.lgnp;
+  const int a = blockIdx.x, tid = threadIdx.x;
   const int64_t v = blockIdx.y;
-  const int64_t row = (b_begin + v) * ld.n;
   // coordinates past the layer's end read its last one (always valid) and are replaced by zero,
   // a select rather than a branch per element
   // (N' <= 2^21: coordinates fit 32-bit offsets from the row's uniform base)
+  const int64_t row = (b_begin + v) * ld.n;
   const uint16_t *xh = (const uint16_t *)x + row;
   const float *xf = (const float *)x + row;
   const uint32_t nlast = (uint32_t)(ld.n - 1);
-  float xv[32];
+  const uint32_t jt = fjl_coord(tid, B) + ((uint32_t)a << B);
+  float e[32];
 #pragma unroll
   for (int m = 0; m < 32; ++m) {
-    const int k = threadIdx.x + 256 * m;
-    const uint32_t j = ((uint32_t)(k >> B) << 13) + ((uint32_t)a << B) + (uint32_t)(k & ((1 << B) - 1));
+    const uint32_t j = jt + fjl_coord(256 * m, B);
     const uint32_t jc = j < nlast ? j : nlast;
     const float t = BF16 ? bf16_to_f32(xh[jc]) : xf[jc];
-    xv[m] = j <= nlast ? t : 0.0f;
+    e[m] = j <= nlast ? t : 0.0f;
   }
-  {
-    const int w = threadIdx.x;
-    const int64_t j = ((int64_t)(w >> (B - 5)) << 13) + ((int64_t)a << B) + ((w & ((1 << (B - 5)) - 1)) << 5);
-    sw[w] = sign_word((uint64_t)j, (uint32_t)ld.layer_id, key);
+  const uint32_t word = fjl_sign_word(a, B, (uint32_t)ld.layer_id, key);
+#pragma unroll
+  for (int m = 0; m < 32; ++m) e[m] = fjl_signed(e[m], word, m);
+  fwht_regs_t<32>(e);
+#pragma unroll
+  for (int m = 0; m < 32; ++m) tile[tid + 260 * m] = e[m];
+  const float *g = gtab + (int64_t)layer * D;
+  uint32_t q[R];
+  float gr[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = tid + 256 * r, ic = i < D ? i : D - 1;
+    q[r] = bpos[ic];
+    gr[r] = g[ic];
   }
   __syncthreads();
-#pragma unroll
-  for (int m = 0; m < 32; ++m) {
-    const int k = threadIdx.x + 256 * m;
-    tile[p16(k)] = flip(xv[m], (sw[k >> 5] >> (k & 31)) & 1u);
-  }
-  lds_fwht_regs(tile, 13, 0);  // opens and closes with a barrier
-  const float *g = gtab + (int64_t)layer * D;
+  fjl_low_bits(tile);
+  __syncthreads();
   float *o = part + ((int64_t)a * bc + v) * D;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int i = threadIdx.x + 256 * r;
-    if (i < D) {
-      const uint32_t q = bpos[i];
-      o[i] = flip(tile[p16((int)(q >> 8))], (uint32_t)__popc((uint32_t)a & q & 255u) & 1u) * (g[i] * scale);
-    }
+    const int i = tid + 256 * r;
+    const float y = tile[fjl_at((int)(q[r] >> 8))];
+    if (i < D) o[i] = flip(y, (uint32_t)__popc((uint32_t)a & q[r] & 255u) & 1u) * (gr[r] * scale);
   }
 }
 
@@ -1699,11 +1778,10 @@ void launch_fjl_fwd_onepass(const sk_sketch *s, int layer, const void *x, int dt
                             float *part, hipStream_t st) {
   const LayerDesc &ld = s->layers[layer];
   const int H = ld.lgnp - 13;
-  const size_t shm = sizeof(float) * p16_floats(1 << 13) + sizeof(uint32_t) * 256;
   const float scale = (float)(1.0 / std::sqrt((double)s->D));
   const uint32_t *bpos = s->d_fjlb_pos + s->fjlb_pos_at[layer];
 #define SK_FJLF1(BF, R)                                                                                          \
-  hipLaunchKernelGGL((k_fjl_fwd_onepass<BF, R>), dim3(1u << H, (unsigned)bc), dim3(256), shm, st, s->d_layers,     \
+  hipLaunchKernelGGL((k_fjl_fwd_onepass<BF, R>), dim3(1u << H, (unsigned)bc), dim3(256), 0, st, s->d_layers,       \
                      layer, s->d_gtab, bpos, x, (int)s->D, b_begin, bc, part, scale, s->key)
   if (dtype == SK_BF16) {
     if (s->D <= 4096) SK_FJLF1(true, 16); else SK_FJLF1(true, 32);
@@ -1718,12 +1796,12 @@ void launch_fjl_T_onepass(const sk_sketch *s, int layer, const float *z, int64_t
                           int out_dtype, const float *theta0, hipStream_t st) {
   const LayerDesc &ld = s->layers[layer];
   const int H = ld.lgnp - 13;
-  const size_t shm = sizeof(float) * p16_floats(1 << 13) + sizeof(uint32_t) * 256;
   const float scale = (float)(1.0 / std::sqrt((double)s->D));
 #define SK_FJLT1(R)                                                                                              \
-  hipLaunchKernelGGL(k_fjl_T_onepass<R>, dim3(1u << H, (unsigned)bc), dim3(256), shm, st, s->d_layers, layer,      \
-                     s->d_gtab, s->d_fjlb_off + s->fjlb_off_at[layer], s->d_fjlb_ent + s->fjlb_ent_at[layer], z,   \
-                     (int)s->D, b_begin, out, out_dtype, theta0, scale, s->key)
+  hipLaunchKernelGGL(k_fjl_T_onepass<R>, dim3(1u << H, (unsigned)bc), dim3(256), 0, st, s->d_layers, layer,        \
+                     s->d_gtab, s->d_fjlb_ent + s->fjlb_pos_at[layer], s->d_fjlb_id + s->fjlb_pos_at[layer],       \
+                     s->d_fjlb_off + s->fjlb_off_at[layer], z, (int)s->D,                                          \
+                     b_begin, out, out_dtype, theta0, scale, s->key)
   if (s->D <= 4096)
     SK_FJLT1(16);
   else

@@ -94,12 +94,11 @@ struct sk_sketch {
   // holds their position (ids and positions, D each) and the blocks' first entries (+ end)
   uint32_t *d_fjl_lsmp = nullptr, *d_fjl_lpos = nullptr, *d_fjl_loff = nullptr;
   std::vector<int64_t> fjl_loff_at;
-  // one-pass FJL transpose (2^14 <= N' <= 2^21): per layer, the samples sorted by tile cell
-  // (top bits, low bits), entry (id << 8) | middle bits, with 2^13 + 1 cell offsets
-  uint32_t *d_fjlb_off = nullptr, *d_fjlb_ent = nullptr;
-  std::vector<int64_t> fjlb_off_at, fjlb_ent_at;
-  // and for the one-pass forward, each sample's (cell << 8) | middle bits, by id
-  uint32_t *d_fjlb_pos = nullptr;
+  // one-pass FJL (2^14 <= N' <= 2^21): per layer, each sample's (cell << 8) | middle bits by id
+  // (forward), and by rank in its cell with the ids and the ranks' first entries (transpose)
+  uint32_t *d_fjlb_pos = nullptr, *d_fjlb_ent = nullptr, *d_fjlb_off = nullptr;
+  uint16_t *d_fjlb_id = nullptr;
+  std::vector<int64_t> fjlb_off_at;
   std::vector<int64_t> fjlb_pos_at;
   // QK
   float *d_qka = nullptr;       // A factors, fp32
