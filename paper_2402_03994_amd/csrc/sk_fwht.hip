@@ -678,22 +678,31 @@ __global__ __launch_bounds__(256, 4) void k_afjl_tail_reg(const LayerDesc *__res
   for (int j = 0; j < J; ++j) o[(int64_t)j * Lw] = acc[j] * sc;
 }
 
-// R = Lw = 1024 with 1024 threads: workgroup per (32 columns, vector), so every
-// partial and G row piece is a full 128-byte line; thread (hi, c) holds rows
-// hi * 32 + j of column c0 + c, H_R = H_32 (x) H_32 with one LDS transpose
-// (128 KB); four waves per SIMD hide the load latency.
-__global__ __launch_bounds__(1024) void k_afjl_tail_1024w(const LayerDesc *__restrict__ layers,
-                                                          const int2 *__restrict__ rslot,
-                                                          const int32_t *__restrict__ rfirst,
-                                                          const float *__restrict__ part,
-                                                          const float *__restrict__ gtab, int l_begin, int l_end,
-                                                          int item_begin, int64_t D, int64_t bc, int64_t b_begin,
-                                                          float *__restrict__ out, int accumulate) {
-  __shared__ float s[1024 * 32];
+// Tail for 128 <= R <= 1024 (Lw = 1024), R threads: a workgroup per 32 columns,
+// vector and group of layers, so that every partial and G row piece is a full
+// 128-byte line; thread (hi, c) holds rows hi * 32 + j of column c0 + c, H_R =
+// H_{R/32} (x) H_32 with one LDS transpose (128 R bytes).  A group's sum goes
+// to slot gi of dst (one group: straight to the output).
+// R < 1024 went through LDS passes over a 4096-value tile, every partial and G
+// load waited for, one workgroup per tile walking all layers: 1920 us of an S
+// H S^T of 8 GPT-2 blocks (one vector, D = 2^18), 2490 -> 579 us as a whole.
+// 4 blocks of width 500 forward, 1 / 8 / 32 vectors: 926 / 933 / 3475 -> 66 /
+// 202 / 808 us at D = 2^18.  R = 1024 had one group: a 2048-wide decoder block
+// of one vector 136 -> 90 us, 8 vectors (256 workgroups) alike.
+template <int R>
+__global__ __launch_bounds__(R) void k_afjl_tail_wide(const LayerDesc *__restrict__ layers,
+                                                      const int2 *__restrict__ rslot,
+                                                      const int32_t *__restrict__ rfirst,
+                                                      const float *__restrict__ part, const float *__restrict__ gtab,
+                                                      TailGroups grp, int item_begin, int64_t D, int64_t bc,
+                                                      float *__restrict__ dst, int64_t slot, int accumulate) {
+  constexpr int HI = R / 32, JJ = 32 / HI;
+  __shared__ float s[R * 32];
   const int c = threadIdx.x & 31, hi = threadIdx.x >> 5;
   // workgroup x runs on XCD x mod 8: each XCD takes 4 consecutive column blocks
   const int c0 = ((blockIdx.x & 7) * 4 + (blockIdx.x >> 3)) * 32;
   const int64_t bl = blockIdx.y;
+  const int l_begin = grp.bound[blockIdx.z], l_end = grp.bound[blockIdx.z + 1];
   float acc[32];
 #pragma unroll
   for (int j = 0; j < 32; ++j) acc[j] = 0.0f;
@@ -703,30 +712,49 @@ __global__ __launch_bounds__(1024) void k_afjl_tail_1024w(const LayerDesc *__res
     // the G loads go out while the partials are in flight (one memory
     // latency per layer), through a buffer resource with scalar row offsets
     const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gtab + (int64_t)l * D, (uint32_t)(D * 4));
-    const int goff = (hi * 1024 + c0 + c) * 4;
+    const int goff = (hi * JJ * 1024 + c0 + c) * 4;
     const LayerDesc &ld = layers[l];
     tail_gather<32>(ld.rmaxch, rs + hi * 32, rfirst + ld.rslot_off + hi * 32, tail_part_rsrc(ld, part, item_begin, bc, 1024, 1),
                     (uint32_t)(bc * 1024 * 4), (uint32_t)((bl * 1024 + c0 + c) * 4), ld.item_off, 1, 0, 1, v);
+    // after the transpose value jj HI + h is row 32 h + hi JJ + jj
 #pragma unroll
-    for (int j = 0; j < 32; ++j) gv[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, goff, j * 32 * 4096, 0));
+    for (int j = 0; j < 32; ++j)
+      gv[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, goff, ((j % HI) * 32 + j / HI) * 4096, 0));
     fwht_regs_t<32>(v);
 #pragma unroll
     for (int j = 0; j < 32; ++j) s[(hi * 32 + j) * 32 + c] = v[j];
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 32; ++j) v[j] = s[(j * 32 + hi) * 32 + c];
+    for (int j = 0; j < 32; ++j) v[j] = s[((j % HI) * 32 + hi * JJ + j / HI) * 32 + c];
     __syncthreads();
-    fwht_regs_t<32>(v);
+#pragma unroll
+    for (int jj = 0; jj < JJ; ++jj) fwht_regs_t<HI>(v + jj * HI);
 #pragma unroll
     for (int j = 0; j < 32; ++j) acc[j] += gv[j] * v[j];
   }
-  float *o = out + (b_begin + bl) * D + c0 + c;
+  const float sc = rsqrtf((float)R);
+  float *o = dst + blockIdx.z * slot + bl * D + hi * JJ * 1024 + c0 + c;
 #pragma unroll
   for (int j = 0; j < 32; ++j) {
-    const int64_t r = j * 32 + hi;
-    const float val = acc[j] * (1.0f / 32.0f);
-    o[r * 1024] = accumulate ? o[r * 1024] + val : val;
+    float *p = o + ((j % HI) * 32 + j / HI) * 1024;
+    const float val = acc[j] * sc;
+    *p = accumulate ? *p + val : val;
   }
+}
+
+// Contiguous groups of layers of about equal live destination rows, at most G; returns their number.
+static int tail_groups(const sk_sketch *s, int l_begin, int l_end, int G, TailGroups &grp) {
+  int64_t total = 0;
+  for (int l = l_begin; l < l_end; ++l) total += s->layers[l].n_items;
+  int ng = 0;
+  grp.bound[0] = l_begin;
+  int64_t accw = 0;
+  for (int l = l_begin; l < l_end; ++l) {
+    accw += s->layers[l].n_items;
+    if (ng < G - 1 && accw * G >= total * (ng + 1) && l + 1 < l_end) grp.bound[++ng] = l + 1;
+  }
+  grp.bound[++ng] = l_end;
+  return ng;
 }
 
 void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin, int split, const float *part,
@@ -735,29 +763,36 @@ void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin
   bool small_parts = true;
   for (int l = l_begin; l < l_end; ++l)
     small_parts = small_parts && (int64_t)s->layers[l].n_items * split * bc * s->Lw * 4 < (1ll << 31);
-  if (s->R == 1024 && s->Lw == 1024 && small_parts) {
+  if (s->R >= 128 && s->Lw == 1024 && small_parts) {
     const int64_t rows = (batch - b_begin) < bc ? (batch - b_begin) : bc;
-    hipLaunchKernelGGL(k_afjl_tail_1024w, dim3(32u, (unsigned)rows), dim3(1024), 0, st, s->d_layers, s->d_rslot,
-                       s->d_rfirst, part, s->d_gtab, l_begin, l_end, item_begin, s->D, bc, b_begin, out,
-                       (int)accumulate);
+    // layer groups until the workgroups (32 per vector and group) fill the CUs, 1024 / R each by LDS
+    TailGroups grp{};
+    const int64_t want = 256 * (1024 / s->R) / (32 * rows);
+    const int ng = tail_groups(s, l_begin, l_end,
+                               (int)std::max<int64_t>(1, std::min<int64_t>({want, kTailGroups, l_end - l_begin})), grp);
+    float *ysum = s->ws + (s->ws_bytes / 4 - (int64_t)kTailGroups * bc * s->D);
+    float *dst = ng == 1 ? out + b_begin * s->D : ysum;
+    const int acc = ng == 1 && accumulate;
+#define SK_TAILW(RR)                                                                                             \
+  case RR:                                                                                                       \
+    hipLaunchKernelGGL(k_afjl_tail_wide<RR>, dim3(32u, (unsigned)rows, (unsigned)ng), dim3(RR), 0, st,           \
+                       s->d_layers, s->d_rslot, s->d_rfirst, part, s->d_gtab, grp, item_begin, s->D, bc, dst,    \
+                       rows * s->D, acc);                                                                        \
+    break;
+    switch (s->R) {
+      SK_TAILW(128) SK_TAILW(256) SK_TAILW(512) SK_TAILW(1024)
+      default: break;
+    }
+#undef SK_TAILW
+    if (ng > 1) launch_reduce_partials(ysum, ng, rows, s->D, b_begin, out, accumulate, st);
     SK_CHECK_LAUNCH();
     return;
   }
   const int R = s->R, Lw = s->Lw;
   if (R <= 64 && small_parts) {
-    // balance the layer loop: groups of about equal live destination rows
+    // balance the layer loop
     TailGroups grp{};
-    int64_t total = 0;
-    for (int l = l_begin; l < l_end; ++l) total += s->layers[l].n_items;
-    const int G = std::min(kTailGroups, l_end - l_begin);
-    int ng = 0;
-    grp.bound[0] = l_begin;
-    int64_t accw = 0;
-    for (int l = l_begin; l < l_end; ++l) {
-      accw += s->layers[l].n_items;
-      if (ng < G - 1 && accw * G >= total * (ng + 1) && l + 1 < l_end) grp.bound[++ng] = l + 1;
-    }
-    grp.bound[++ng] = l_end;
+    const int ng = tail_groups(s, l_begin, l_end, std::min(kTailGroups, l_end - l_begin), grp);
     float *ysum = s->ws + (s->ws_bytes / 4 - (int64_t)kTailGroups * bc * s->D);
     // split items of a call with few layers: the shares over what is left of the 16 sums, each through H_R
     // and G by itself (a head of 4 layers in 16 shares: this kernel 9.6 -> 4.9 us)
