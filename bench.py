@@ -51,7 +51,7 @@ KERNEL_OF = {"affd:affd_rows": "k_affdT_rows", "afjl:afjl_fold": "k_afjl_fold", 
              "ffd:ffd": "k_ffd_small_fwd", "ffd:gather": "k_reduce_partials", "fjl:prolog": "k_fjl_fwd_onepass",
              "afjlq:qh_first": "k_qh_gemm", "qkh:qh_first": "k_qh_gemm", "afjlq:qh_second": "k_qh_gemm",
              "qkh:qh_second": "k_qh_gemm", "affdq:qh_first": "k_qh_gemm", "affdq:qh_t": "k_qh_gemm",
-             "hvp:hvp_dots": "k_hvp_dots", "hvp:hvp_combine": "k_hvp_combine", "afjl:gather": "k_afjl_T_out",
+             "hvp:hvp_dots": "k_hvp_dots", "hvp:hvp_combine": "k_hvp_combine", "afjl:gather": "k_afjl_unfold",
              "ffd:ffd_t": "k_ffd_small_T", "afjlf:ff_rows": "k_ffr_fwd", "afjlf:ff_small": "k_ffs_fwd",
              "afjlf:ff_res": "k_ffq_fwd", "affd:affd_fold": "k_affdT_topM", "afjl:afjl_tail": "k_afjl_tail",
              "affd:gather": "k_affdT_outm", "ffd:prolog": "k_ffd_tables",
@@ -115,8 +115,9 @@ def qh_flops(kind, shapes, D):
 
 # kernel sources behind each kind (the shared headers and the dispatcher are hashed for every config)
 _COMMON_SRC = ("sk_api.hip", "sk_internal.h", "sk_launch.h", "sk_kcommon.h", "sk_device.h")
-_KIND_SRC = {"fjl": ("sk_fwht.hip",), "ffd": ("sk_fwht.hip", "sk_ffd_l.hip"), "afjl": ("sk_fwht.hip",),
-             "affd": ("sk_fwht.hip", "sk_affd.hip", "sk_affd_s.hip", "sk_affd_t.hip"), "qk": ("sk_qk.hip",),
+_KIND_SRC = {"fjl": ("sk_fwht.hip",), "ffd": ("sk_fwht.hip", "sk_ffd_m.hip", "sk_ffd_l.hip"), "afjl": ("sk_fwht.hip",),
+             "affd": ("sk_fwht.hip", "sk_affd.hip", "sk_affd_s.hip", "sk_affd_t.hip", "sk_affd_tt.hip"),
+             "qk": ("sk_qk.hip", "sk_qk64.hip"),
              "qkh": ("sk_qhaar.hip",), "afjlq": ("sk_qhaar.hip",), "affdq": ("sk_qhaar.hip",),
              "afjlf": ("sk_afjlf.hip", "sk_fft.h")}
 
