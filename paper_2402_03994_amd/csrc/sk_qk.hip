@@ -487,13 +487,18 @@ bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t bc) {
   return bc > 1 && (qk_afirst_ok(ld, dtype) || qk_mfma_ok(ld, dtype));
 }
 
+// First products held by a group: half of the memory-side cache, so that the second contraction finds them there.
+// A layer that fills the chip alone needs no group: 145 matrices of a 2048-wide decoder, 256 vectors, took
+// 154 to 160 ms in groups of up to 32 (33 to 268 MB of first products each), 156.5 layer by layer, 152.6 so.
+constexpr int64_t kQkGroupBytes = 128ll << 20;
+
 QkGroup qk_group(const sk_sketch *s, const int *layers, int count, int64_t bc, int64_t ws_bytes) {
   QkGroup g{};
   int64_t off = 0;
   while (g.n < count && g.n < kQkTasks) {
     const LayerDesc &ld = s->layers[layers[g.n]];
     const int64_t need = bc * (qk_afirst_ok(ld, SK_BF16) ? (int64_t)ld.da * ld.nc : (int64_t)ld.m * ld.db);
-    if (g.n && (off + need) * 4 > ws_bytes) break;
+    if (g.n && (off + need) * 4 > std::min(ws_bytes, kQkGroupBytes)) break;
     g.layer[g.n] = layers[g.n];
     g.t_off[g.n] = off;
     off += (need + 3) & ~3ll;
