@@ -10,7 +10,7 @@
 //               -> columns, theta0, written
 // The gather stays inside one block (64 KB to 2 MB), whose workgroups are
 // placed on one XCD (workgroups go to the XCDs in turn) so that it hits that
-// XCD's L2.  The Feistel network's eight round functions depend on one half of
+// XCD's L2, unless that leaves the device idle (local_blocks).  The Feistel network's eight round functions depend on one half of
 // the index only, so a workgroup tabulates them in LDS (2 KB to 12 KB, where
 // the row tile goes afterwards: 1 k to 6 k hashes for its 8192 coordinates
 // instead of 64 k; two 32-bit multiplies per hash made the permutation the
@@ -28,9 +28,16 @@ namespace sk {
 
 namespace {
 
-// Workgroup -> (block b, part t of T): the T parts of a block on one XCD.
-// False past the last block (the grid covers blocks rounded up to 8).
-__device__ __forceinline__ bool place(uint32_t id, uint32_t T, int64_t nblk, int64_t &b, int &t) {
+// Workgroup -> (block b, part t of T): the T parts of each of the first
+// `local` blocks (a multiple of 8) on one XCD, those of the others in a row.
+// False past the last block.
+__device__ __forceinline__ bool place(uint32_t id, uint32_t T, int64_t nblk, int64_t local, int64_t &b, int &t) {
+  if (id >= (uint32_t)local * T) {
+    const uint32_t e = id - (uint32_t)local * T;
+    b = local + e / T;
+    t = (int)(e % T);
+    return b < nblk;
+  }
   const uint32_t q = id >> 3;
   b = (int64_t)(q / T) * 8 + (id & 7);
   t = (int)(q % T);
@@ -88,7 +95,8 @@ enum { kRowsX = 0, kRowsZ = 1, kRowsInv = 2, kRowsFwd = 3 };
 template <int SRC, bool BF16>
 __global__ __launch_bounds__(256, SRC == kRowsFwd ? 3 : 4) void k_ffdM_rows(const LayerDesc *__restrict__ layers, int layer,
                                                    const void *__restrict__ src, int lgD, int64_t nblk,
-                                                   int64_t b_begin, int64_t bc, float *__restrict__ w, Key key) {
+                                                   int64_t local, int64_t b_begin, int64_t bc, float *__restrict__ w,
+                                                   Key key) {
   typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
   typedef uint16_t h4u __attribute__((ext_vector_type(4), aligned(2)));
   using L = Lds1024<8>;
@@ -97,7 +105,7 @@ __global__ __launch_bounds__(256, SRC == kRowsFwd ? 3 : 4) void k_ffdM_rows(cons
   const LayerDesc &ld = layers[layer];
   int64_t b;
   int t;
-  if (!place(blockIdx.x, 1u << (lgD - 13), nblk, b, t)) return;  // uniform
+  if (!place(blockIdx.x, 1u << (lgD - 13), nblk, local, b, t)) return;  // uniform
   const int64_t D = 1ll << lgD;
   const int col = 4 * threadIdx.x;
   const int i0 = t * 8192;  // first coordinate of the rows, within the block
@@ -230,14 +238,14 @@ struct Tile {
 // In place: H_R along the rows, times g (forward).
 template <int LGD, bool G>
 __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_cols(const LayerDesc *__restrict__ layers, int layer,
-                                                                   int64_t nblk, int64_t bc, float *__restrict__ w,
-                                                                   Key key) {
+                                                                   int64_t nblk, int64_t local, int64_t bc,
+                                                                   float *__restrict__ w, Key key) {
   using T = Tile<LGD>;
   __shared__ __align__(16) float s[T::FLOATS];
   const LayerDesc &ld = layers[layer];
   int64_t b;
   int t;
-  if (!place(blockIdx.x, T::TILES, nblk, b, t)) return;
+  if (!place(blockIdx.x, T::TILES, nblk, local, b, t)) return;
   const int c0 = t << T::LGCS;
   float x[T::NE];
   int64_t v = blockIdx.y;
@@ -272,15 +280,15 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_cols(const LayerDe
 // Transpose, last pass: H_R, 1/D, theta0, the layer's outputs.
 template <int LGD>
 __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_out(const LayerDesc *__restrict__ layers, int layer,
-                                                                  int64_t nblk, int64_t b_begin, int64_t bc,
-                                                                  const float *__restrict__ w, void *__restrict__ out,
+                                                                  int64_t nblk, int64_t local, int64_t b_begin,
+                                                                  int64_t bc, const float *__restrict__ w, void *__restrict__ out,
                                                                   int out_dtype, const float *__restrict__ theta0) {
   using T = Tile<LGD>;
   __shared__ __align__(16) float s[T::FLOATS];
   const int64_t n = layers[layer].n;
   int64_t b;
   int t;
-  if (!place(blockIdx.x, T::TILES, nblk, b, t)) return;
+  if (!place(blockIdx.x, T::TILES, nblk, local, b, t)) return;
   const int64_t j0 = b << LGD;
   const int lim = (int)(n - j0 < (1ll << LGD) ? n - j0 : 1ll << LGD);  // entries of the block
   const int i0 = T::place1() + (t << T::LGCS);
@@ -374,7 +382,16 @@ namespace {
 unsigned shares(int64_t blocks, int64_t bc) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(bc, 2048 / std::max<int64_t>(1, blocks)));
 }
-int64_t up8(int64_t n) { return (n + 7) & ~7ll; }
+// Blocks whose parts share an XCD (place); the grid has max(nblk, local) blocks.  Beyond the last eight, one to three
+// blocks on an XCD each leave most of the device idle, which costs more than a gather outside the XCD's L2 once the
+// call has 2^19 values per block: D = 2^19, one block, 1 / 4 / 16 vectors, transpose: 73 / 174 / 617 us on one XCD, 57 /
+// 75 / 161 spread; nine blocks of 2^17, 16 vectors, 258 / 178.  Fewer values stay in L2 (D = 2^16, one block, one vector
+// 32.5 / 38), and four blocks or more fill enough of the device (D = 2^18, four, 16 vectors forward 258 / 292; D = 2^17,
+// seven, 4 vectors 61 / 79).
+int64_t local_blocks(int64_t nblk, int64_t D, int64_t bc) {
+  const int64_t rest = nblk & 7;
+  return rest <= 3 && D * bc >= 1 << 19 ? nblk - rest : (nblk + 7) & ~7ll;
+}
 }  // namespace
 
 bool ffd_mid_path(const sk_sketch *s) { return s->D > (1ll << kFfdSmallMax) && s->D < (1ll << 20); }
@@ -398,25 +415,26 @@ void run_ffd_mid_fwd(const sk_sketch *s, int layer, const void *x, int dtype, in
   int lgD = 14;
   while ((1ll << lgD) < s->D) ++lgD;
   const int64_t nblk = ffd_live_blocks(s, layer);
+  const int64_t local = local_blocks(nblk, s->D, bc), gblk = std::max(nblk, local);
   float *w = s->ws, *w2 = s->ws + bc * nblk * s->D;
-  const int64_t rgrid = up8(nblk) << (lgD - 13);
+  const int64_t rgrid = gblk << (lgD - 13);
   const dim3 gr((unsigned)rgrid, shares(rgrid, bc));
   if (phases & 1) {
     if (dtype == SK_BF16)
-      hipLaunchKernelGGL((k_ffdM_rows<kRowsX, true>), gr, dim3(256), 0, st, s->d_layers, layer, x, lgD, nblk, b_begin,
-                         bc, w, s->key);
+      hipLaunchKernelGGL((k_ffdM_rows<kRowsX, true>), gr, dim3(256), 0, st, s->d_layers, layer, x, lgD, nblk, local,
+                         b_begin, bc, w, s->key);
     else
-      hipLaunchKernelGGL((k_ffdM_rows<kRowsX, false>), gr, dim3(256), 0, st, s->d_layers, layer, x, lgD, nblk,
+      hipLaunchKernelGGL((k_ffdM_rows<kRowsX, false>), gr, dim3(256), 0, st, s->d_layers, layer, x, lgD, nblk, local,
                          b_begin, bc, w, s->key);
   }
   if (!(phases & 2)) return;
   with_lgD(lgD, [&](auto lg) {
     constexpr int LGD = decltype(lg)::value;
-    const int64_t tiles = Tile<LGD>::TILES, cgrid = up8(nblk) * tiles;
+    const int64_t tiles = Tile<LGD>::TILES, cgrid = gblk * tiles;
     hipLaunchKernelGGL((k_ffdM_cols<LGD, true>), dim3((unsigned)cgrid, shares(cgrid, bc)), dim3(256), 0, st,
-                       s->d_layers, layer, nblk, bc, w, s->key);
-    hipLaunchKernelGGL((k_ffdM_rows<kRowsInv, false>), gr, dim3(256), 0, st, s->d_layers, layer, w, lgD, nblk, b_begin,
-                       bc, w2, s->key);
+                       s->d_layers, layer, nblk, local, bc, w, s->key);
+    hipLaunchKernelGGL((k_ffdM_rows<kRowsInv, false>), gr, dim3(256), 0, st, s->d_layers, layer, w, lgD, nblk, local,
+                       b_begin, bc, w2, s->key);
     // runs of blocks: 1024 workgroups while each has a block; the partial sums take the place of w
     int64_t runs = std::max<int64_t>(1, std::min<int64_t>(nblk, 1024 / std::max<int64_t>(1, tiles * bc)));
     const int64_t per = (nblk + runs - 1) / runs;
@@ -432,23 +450,24 @@ void run_ffd_mid_T(const sk_sketch *s, int layer, const float *z, int64_t b_begi
   int lgD = 14;
   while ((1ll << lgD) < s->D) ++lgD;
   const int64_t nblk = ffd_live_blocks(s, layer);
+  const int64_t local = local_blocks(nblk, s->D, bc), gblk = std::max(nblk, local);
   float *w = s->ws, *w2 = s->ws + bc * nblk * s->D;
-  const int64_t rgrid = up8(nblk) << (lgD - 13);
+  const int64_t rgrid = gblk << (lgD - 13);
   const dim3 gr((unsigned)rgrid, shares(rgrid, bc));
   with_lgD(lgD, [&](auto lg) {
     constexpr int LGD = decltype(lg)::value;
-    const int64_t cgrid = up8(nblk) * Tile<LGD>::TILES;
+    const int64_t cgrid = gblk * Tile<LGD>::TILES;
     const dim3 gc((unsigned)cgrid, shares(cgrid, bc));
     if (phases & 1) {
-      hipLaunchKernelGGL((k_ffdM_rows<kRowsZ, false>), gr, dim3(256), 0, st, s->d_layers, layer, z, lgD, nblk, b_begin,
-                         bc, w, s->key);
-      hipLaunchKernelGGL((k_ffdM_cols<LGD, false>), gc, dim3(256), 0, st, s->d_layers, layer, nblk, bc, w, s->key);
-      hipLaunchKernelGGL((k_ffdM_rows<kRowsFwd, false>), gr, dim3(256), 0, st, s->d_layers, layer, w, lgD, nblk,
+      hipLaunchKernelGGL((k_ffdM_rows<kRowsZ, false>), gr, dim3(256), 0, st, s->d_layers, layer, z, lgD, nblk, local,
+                         b_begin, bc, w, s->key);
+      hipLaunchKernelGGL((k_ffdM_cols<LGD, false>), gc, dim3(256), 0, st, s->d_layers, layer, nblk, local, bc, w, s->key);
+      hipLaunchKernelGGL((k_ffdM_rows<kRowsFwd, false>), gr, dim3(256), 0, st, s->d_layers, layer, w, lgD, nblk, local,
                          b_begin, bc, w2, s->key);
     }
     if (phases & 2)
-      hipLaunchKernelGGL((k_ffdM_out<LGD>), gc, dim3(256), 0, st, s->d_layers, layer, nblk, b_begin, bc, w2, out,
-                         out_dtype, theta0);
+      hipLaunchKernelGGL((k_ffdM_out<LGD>), gc, dim3(256), 0, st, s->d_layers, layer, nblk, local, b_begin, bc, w2,
+                         out, out_dtype, theta0);
   });
 }
 

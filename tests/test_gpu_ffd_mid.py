@@ -42,3 +42,26 @@ def test_ffd_mid(case, dtype, dev, monkeypatch):  # noqa: F811
     for o, r in zip(outs, refs):
         assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL_F32)
     s.close()
+
+
+def parity(lgD, shapes, batch, seed, dtype, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    D = 1 << lgD
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    s = Sketch("ffd", shapes, D, seed, device=dev)
+    xs = rand_inputs(shapes, batch, seed, dtype=tdt)
+    ref = O.apply("ffd", shapes, D, seed, [oracle_in(x)[0] for x in xs], dtype=dtype)
+    assert rel_err(s.apply([x.to(dev) for x in xs]).cpu().numpy(), ref) < TOL_F32
+    g = torch.Generator().manual_seed(seed)
+    z = torch.randn((batch, D), generator=g)
+    outs = s.apply_T(z.to(dev), out_dtype=tdt)
+    refs = O.apply_T("ffd", shapes, D, seed, z.numpy().astype(np.float64))
+    for o, r in zip(outs, refs):
+        assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL_F32)
+    s.close()
+
+
+# blocks beyond the last eight, with 2^19 values per block and call or more: none to seven of them
+@pytest.mark.parametrize("lgD,blocks,batch", [(19, 1, 1), (18, 2, 3), (17, 9, 4), (15, 12, 16), (17, 5, 5), (16, 15, 8)])
+def test_ffd_mid_few_blocks(lgD, blocks, batch, dev):  # noqa: F811
+    parity(lgD, [(1, (blocks << lgD) - 1021)], batch, 800 + lgD + blocks, "f32", dev)
