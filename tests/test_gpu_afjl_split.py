@@ -54,3 +54,18 @@ def test_afjl_transpose_rows(lgD, batch, dtype, dev):  # noqa: F811
     for o, r in zip(outs, refs):
         assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL_F32)
     s.close()
+
+
+# shares of items with 16 rows or more for every R up to 64 (one item per destination row, several layers and one, so
+# that the tail shares them out too), beside layers of one live row and of a part of a destination row's rows
+@pytest.mark.parametrize("lgD,batch", [(11, 1), (13, 3), (14, 1), (14, 9), (15, 1), (15, 2), (16, 1), (16, 3)])
+@pytest.mark.parametrize("layers", [[(1, 2 ** 21 + 5)], [(1, 2), (1025, 1025), (3, 2 ** 20 + 7), (1, 769)]])
+def test_afjl_split_shares(lgD, batch, layers, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    D, seed = 1 << lgD, 70 + lgD
+    xs = rand_inputs(layers, batch, seed, dtype=torch.float32)
+    ref = O.apply("afjl", layers, D, seed, [oracle_in(x)[0] for x in xs], dtype="f32")
+    s = Sketch("afjl", layers, D, seed, device=dev)
+    y = s.apply([x.to(dev) for x in xs])
+    assert rel_err(y.cpu().numpy(), ref) < TOL_F32
+    s.close()
