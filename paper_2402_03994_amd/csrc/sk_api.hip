@@ -734,7 +734,7 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
       case SK_AFJL: {
         // fold launches of at most kMaxPtrs layers, then one tail over all layers
         const int it_base = s->layers[l0].item_off;
-        const int split = afjl_fold_split(s, l0, l1, bc, std::min(bc, batch - b0));
+        const int split = afjl_fold_split(s, l0, l1, esz, bc, std::min(bc, batch - b0));
         for (int g0 = l0; g0 < l1; g0 += kMaxPtrs) {
           const int g1 = std::min(l1, g0 + kMaxPtrs);
           PtrPack pp{};

@@ -436,19 +436,30 @@ __global__ __launch_bounds__(256) void k_afjl_fold1(const FoldItem *__restrict__
 // Workgroups per fold item: the fold's grid is brought to at most 1024
 // workgroups (four per CU, what the kernels' LDS allows) while every share
 // keeps 8 or more rows; partial sums beyond the workspace and the tails for
-// R > 64 (whose items are many and short already) take none.
-int afjl_fold_split(const sk_sketch *s, int l0, int l1, int64_t bc, int64_t rows) {
+// R > 64 (whose items are many and short already) take none.  Nor does a launch
+// whose items times vectors (3072) and bytes (1 GB) keep the memory busy for
+// longer than its longest item takes, where the partials of shares are only
+// more bytes: 3 GPT-2 blocks, D = 2^10, fp32 / bf16, 32 vectors 447 / 252 us
+// unsplit, 523 / 333 split; 20 vectors 380 / 223, 313 / 173.  Items at R = 64
+// are a sixteenth as long, so a share's partial weighs more (four 2048 x 2048,
+// 4 / 8 vectors: 91 / 118 unsplit, 78 / 125 split; a head of width 768, 32
+// vectors, 52 and 59).
+int afjl_fold_split(const sk_sketch *s, int l0, int l1, int esz, int64_t bc, int64_t rows) {
   if (s->R > 64) return 1;
   const int64_t items = s->layers[l1 - 1].item_off + s->layers[l1 - 1].n_items - s->layers[l0].item_off;
-  int64_t most = 0;  // rows of the longest item
+  int64_t most = 0, n = 0;  // rows of the longest item, entries of a vector
   for (int l = l0; l < l1; ++l) {
     const LayerDesc &ld = s->layers[l];
     const int64_t t = s->R == 1 ? ld.rows_live : (ld.rows_live + ld.dk1 - 1) / ld.dk1 * (ld.dk1 / s->R);
     most = std::max(most, std::min<int64_t>(t, kFoldRowsPerItem));
+    n += ld.n;
   }
-  const int64_t blocks = items * (rows == 1 ? 1 : (rows + 7) / 8);
+  const int64_t launches = (l1 - l0 + kMaxPtrs - 1) / kMaxPtrs;
+  const bool r64 = s->R == 64;
+  if (items * rows >= launches * (r64 ? 2048 : 3072) && (r64 || n * rows * esz >= launches << 30)) return 1;
+  const int64_t blocks = items * (rows == 1 ? 1 : (rows + 7) / 8), least = r64 ? 16 : 8;
   int S = 1;
-  while (blocks * S * 2 <= 1024 && most >= 8 * S * 2 &&
+  while (blocks * S * 2 <= 1024 && most >= least * S * 2 &&
          bc * (items * S * 2 * s->Lw + (int64_t)kTailGroups * s->D) * 4 <= s->ws_bytes)
     S *= 2;
   return S;

@@ -79,7 +79,7 @@ void run_afjlf_T(sk_sketch *s, int l0, int l1, const float *z, int64_t b_begin, 
 
 // ---- AFJL ----
 // split: workgroups (and partial sums) per fold item, from afjl_fold_split for the whole call.
-int afjl_fold_split(const sk_sketch *s, int l0, int l1, int64_t bc, int64_t rows);
+int afjl_fold_split(const sk_sketch *s, int l0, int l1, int esz, int64_t bc, int64_t rows);
 void launch_afjl_fold(const sk_sketch *s, const PtrPack &ptrs, int first_layer, int dtype, int64_t batch,
                       int64_t b_begin, int64_t bc, int item_begin, int item_end, int split, float *part,
                       hipStream_t st);
