@@ -483,10 +483,15 @@ __global__ __launch_bounds__(256) void k_qh_mtab(const float *__restrict__ c, in
 int tiles_for(int m) { return m >= 64 ? 4 : m > 16 ? 2 : 1; }
 
 // Waves per workgroup: eight where each still has two steps of 16 or more (K
-// >= 256), else four.  A 600-wide block's weights: one vector 218 -> 136 us at
-// D = 2^14 and 327 -> 237 us at 2^17; 16 vectors at 2^17 (more blocks than CUs
-// already) 520 -> 504 us.
-int waves_for(int k) { return k >= 256 ? 8 : 4; }
+// >= 256) and the workgroups are few, else four.  Eight waves keep a block's
+// loads in flight when a CU has one or two blocks; their partial blocks take
+// 128 KB of LDS, one workgroup per CU, and with more blocks than two per CU two
+// workgroups of four waves hide the reductions of each other.  A 600-wide
+// block's weights, one vector, four / eight waves: 218 / 136 us at D = 2^14, 327
+// / 237 at 2^17.  AFFDQ of a 768-wide block, D = 2^16, 64 vectors, transposed:
+// 24632 / 27406, forward 24591 / 26878; AFJLQ of 2^20 entries, D = 2^20, 8 vectors
+// 340 / 402; a 600-wide block at D = 2^14, 32 vectors (512 blocks) 325 / 277.
+int waves_for(int k, int64_t blocks) { return k >= 256 && blocks <= 512 ? 8 : 4; }
 
 template <int PM, int QM, int PF, int EP, bool SL>
 void launch_tiles(const QhArgs &a, const QhSlots &sl, int mmax, unsigned gy, unsigned gz, hipStream_t st) {
@@ -503,9 +508,9 @@ void launch_tiles(const QhArgs &a, const QhSlots &sl, int mmax, unsigned gy, uns
     else
       hipLaunchKernelGGL((k_qh_gemm<NW, 1, TB, PM, QM, PF, EP, SL>), grid, dim3(64 * NW), 0, st, a, sl);
   };
-  if (QM == kQNT || waves_for(a.K) == 8)  // K = 1024 in the NT forms
+  if (waves_for(a.K, (int64_t)grid.x * gy * gz) == 8)
     go(std::integral_constant<int, 8>{});
-  else if constexpr (QM != kQNT)
+  else
     go(std::integral_constant<int, 4>{});
 }
 

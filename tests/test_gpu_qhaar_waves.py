@@ -30,3 +30,19 @@ def test_k_division(kind, n, D, batch, bf16, dev):  # noqa: F811
     z = torch.randn((batch, D), generator=g)
     out = s.apply_T(z.to(dev))[0].cpu().numpy()
     assert rel_err(out, O.apply_T(kind, [(1, n)], D, 21, z.double().numpy())[0]) < TOL
+
+
+@pytest.mark.parametrize("kind,n,D,batch", [
+    ("afjlq", 2 ** 19 - 3, 1 << 18, 9),   # 576 blocks of K = 512 and 1024: four waves
+    ("affdq", 301 * 1024 + 77, 4096, 9),  # 720 blocks of the stacked rows, 144 to 288 of the others
+    ("qkh", 2 ** 21 + 5, 1 << 16, 33),    # 528 blocks of K = 1024, three slabs
+])
+def test_more_blocks_than_two_per_cu(kind, n, D, batch, dev):  # noqa: F811
+    g = torch.Generator().manual_seed(n)
+    x = torch.randn((batch, n), generator=g)
+    s = sketch(kind, [(1, n)], D, 22, dev)
+    y = s.apply([x.to(dev)]).cpu().numpy()
+    assert rel_err(y, O.apply(kind, [(1, n)], D, 22, [x.numpy()])) < TOL
+    z = torch.randn((batch, D), generator=g)
+    out = s.apply_T(z.to(dev))[0].cpu().numpy()
+    assert rel_err(out, O.apply_T(kind, [(1, n)], D, 22, z.double().numpy())[0]) < TOL
