@@ -588,10 +588,12 @@ void launch_qk_second(const sk_sketch *s, const QkGroup &g, int64_t b_begin, int
       t.db = ld.db;
       t.col = ld.qk_col;
       // ranges of K: 1024 workgroups in the group (four per CU), 512 terms or more each, as far as the partial
-      // sums fit
+      // sums fit.  Blocks of 4 x 4 tiles (64 KB of LDS) that fill the CUs evenly are left whole: a 32000 x 1024
+      // embedding (256, 64), 32 vectors (128 blocks) 1385 us whole and 1168 divided, 64 vectors 2028 and 2189, 96
+      // vectors (384 blocks) 3472 and 3134, 128 vectors 4114 and 4173
       const int64_t cnt = (int64_t)ld.da * ld.db;
       int64_t nk = std::min({t.K / 512, 1024 / total, (s->ws_bytes / 4 - spare) / (bc * cnt)});
-      if (nk < 2) nk = 1;
+      if (nk < 2 || (ta * tb == 16 && total >= 256 && (total + 32) % 256 <= 32)) nk = 1;
       t.kper = ((t.K + nk - 1) / nk + 63) / 64 * 64;
       nk = (t.K + t.kper - 1) / t.kper;
       t.nk = (int)nk;

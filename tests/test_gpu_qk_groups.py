@@ -36,3 +36,15 @@ def test_qk_bf16_groups(batch, ws_mb, dev, monkeypatch):  # noqa: F811
     ref[:, col:] *= 2
     assert rel_err(y.cpu().numpy(), ref) < tol
     s.close()
+
+
+# 4 x 4 tiles per block of the second contraction: divided, but whole with 256 and 480 to 512 blocks
+@pytest.mark.parametrize("batch", [3, 255, 256, 257, 479, 480])
+def test_qk_bf16_whole_blocks(batch, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    shapes, seed = [(2048, 128, 64, 64)], 29
+    s = Sketch("qk", shapes, 64 * 64, seed, device=dev)
+    xs = rand_inputs(shapes, batch, seed, dtype=torch.bfloat16)
+    ref = O.apply("qk", shapes, 64 * 64, seed, [oracle_in(x)[0] for x in xs], dtype="bf16")
+    assert rel_err(s.apply([x.to(dev) for x in xs]).cpu().numpy(), ref) < 1e-4
+    s.close()
