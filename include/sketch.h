@@ -192,9 +192,15 @@ int sketch_create(sk_kind kind, const sk_layer_shape *shapes, int32_t n_layers, 
  *               group).  For QK only the selected layers' column blocks of
  *               `out` are written (or accumulated).
  *   first_layer, n_layers  the contiguous layer range this call covers.
- * Arithmetic is fp32 (bf16 inputs are widened exactly); QK multiplies bf16
- * inputs by the bf16 hi and lo terms of B on the matrix cores with fp32
- * accumulation, then by the fp32 A.
+ * Arithmetic is fp32 (bf16 inputs are widened exactly).  QK sums products with
+ * the fp32 factors in fp64, each of the two contractions rounded once to fp32
+ * (errors of about 1e-7 of the result); only bf16 matrices with cols a multiple
+ * of 128, rows, qk_da and qk_db of 16, qk_db <= 128 (or rows of 64, cols of 256
+ * and qk_da <= 64 below qk_db), in calls of two or more vectors, go through the
+ * bf16 matrix cores: the first factor applied as bf16 hi and lo terms (16
+ * mantissa bits), the second in fp32, fp32 sums (about 3e-6).  So a vector's
+ * result may differ by that much between a call of one vector and a call of
+ * several.
  */
 int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t batch, float *out,
                  int32_t first_layer, int32_t n_layers, int32_t accumulate, void *stream);

@@ -1030,7 +1030,7 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
         break;
       case SK_QK: {
         std::vector<int> bf, rest;  // on the bf16 tiling; off it: fp64 sums
-        for (int l = l0; l < l1; ++l) (qk_bf16_path(s->layers[l], dtype, bc) ? bf : rest).push_back(l);
+        for (int l = l0; l < l1; ++l) (qk_bf16_path(s->layers[l], dtype, batch) ? bf : rest).push_back(l);
         auto bytes_of = [&](const int32_t *ls, int n, const void **x, int64_t &in, int64_t &ob) {
           in = ob = 0;
           for (int j = 0; j < n; ++j) {

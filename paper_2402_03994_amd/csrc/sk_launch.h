@@ -270,8 +270,9 @@ void run_ffd_large_T(const sk_sketch *s, int layer, const float *z, int64_t b_be
 
 // ---- QK ----
 void launch_qk_factors(const sk_sketch *s, hipStream_t st);
-// Does the layer take the bf16 matrix-core contractions in a call of bc vectors?  (Else: the fp64-sum ones below.)
-bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t bc);
+// Does the layer take the bf16 matrix-core contractions in a call of `batch` vectors, however the workspace divides
+// them?  (Else: the fp64-sum ones below.)
+bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t batch);
 // Tasks of a launch, by value in the kernel arguments (under 4 KB).
 constexpr int kQkTasks = 32;
 struct QkFirstTask {

@@ -478,13 +478,16 @@ bool qk_mfma_ok(const LayerDesc &ld, int dtype) {
   return dtype == SK_BF16 && ld.nc % 128 == 0 && ld.m % 16 == 0 && ld.da % 16 == 0 && ld.db % 16 == 0 && ld.db <= 128;
 }
 
-// One vector goes through the fp64-sum kernels: their workgroups split the
-// contraction over four waves, and the length of one chain is what counts (12
-// GPT-2 blocks of width 768: 270 against 377 us; 2048-wide decoder block 125
-// against 172; two vectors 400 against 443, 163 against 175, but 181 against 131
-// for four blocks of width 1024).
-bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t bc) {
-  return bc > 1 && (qk_afirst_ok(ld, dtype) || qk_mfma_ok(ld, dtype));
+// A call of one vector goes through the fp64-sum kernels: their workgroups
+// split the contraction over four waves, and the length of one chain is what
+// counts (fp64 sums / bf16, one vector: 12 GPT-2 blocks of width 768 250 / 398
+// us, a 2048-wide decoder block 125 / 172, 8192 x 8192 (128, 128) 331 / 584).
+// Layers that fill the device by themselves would be faster here (32768 x 768
+// (64, 16) 49 / 36, 50304 x 2048 (256, 64) 307 / 148, 128256 x 4096 (256, 64)
+// 1184 / 401), but with the first factor to 16 bits: errors of 2.5e-6 instead of
+// 1e-7.  Two vectors: 400 / 443 (12 blocks), but 181 / 131 (4 of width 1024).
+bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t batch) {
+  return batch > 1 && (qk_afirst_ok(ld, dtype) || qk_mfma_ok(ld, dtype));
 }
 
 // First products held by a group: half of the memory-side cache, so that the second contraction finds them there.

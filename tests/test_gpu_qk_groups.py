@@ -48,3 +48,17 @@ def test_qk_bf16_whole_blocks(batch, dev):  # noqa: F811
     ref = O.apply("qk", shapes, 64 * 64, seed, [oracle_in(x)[0] for x in xs], dtype="bf16")
     assert rel_err(s.apply([x.to(dev) for x in xs]).cpu().numpy(), ref) < 1e-4
     s.close()
+
+
+# A workspace of two vectors: the last vector of a call of three is alone in its chunk and still sees B as two bf16
+# terms.  With one entry every sum has one product, so that equal vectors agree bit for bit.
+def test_qk_bf16_last_chunk(dev, monkeypatch):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    monkeypatch.setenv("SK_WORKSPACE_MB", "16")
+    shape = (16384, 128, 16, 128)
+    s = Sketch("qk", [shape], 16 * 128, 33, device=dev)
+    x = torch.zeros((3, 16384 * 128), dtype=torch.bfloat16, device=dev)
+    x[:, 5 * 128 + 7] = 1.0
+    y = s.apply([x])
+    assert y.abs().max() > 0 and torch.equal(y[0], y[1]) and torch.equal(y[0], y[2])
+    s.close()
