@@ -114,7 +114,7 @@ def qh_flops(kind, shapes, D):
 
 
 # kernel sources behind each kind (the shared headers and the dispatcher are hashed for every config)
-_COMMON_SRC = ("sk_api.hip", "sk_internal.h", "sk_launch.h", "sk_kcommon.h", "sk_device.h")
+_COMMON_SRC = ("sk_api.hip", "sk_internal.h", "sk_launch.h", "sk_grid.h", "sk_kcommon.h", "sk_device.h")
 _KIND_SRC = {"fjl": ("sk_fwht.hip",), "ffd": ("sk_fwht.hip", "sk_ffd_m.hip", "sk_ffd_l.hip"), "afjl": ("sk_fwht.hip",),
              "affd": ("sk_fwht.hip", "sk_affd.hip", "sk_affd_s.hip", "sk_affd_t.hip", "sk_affd_tt.hip"),
              "qk": ("sk_qk.hip", "sk_qk64.hip"),

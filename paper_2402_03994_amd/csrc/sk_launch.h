@@ -1,6 +1,7 @@
 // sk_launch.h -- host-side launchers of the sketch kernels (one per kernel).
 #pragma once
 
+#include "sk_grid.h"
 #include "sk_internal.h"
 
 namespace sk {
@@ -275,6 +276,7 @@ void launch_qk_factors(const sk_sketch *s, hipStream_t st);
 bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t batch);
 // Tasks of a launch, by value in the kernel arguments (under 4 KB).
 constexpr int kQkTasks = 32;
+constexpr int64_t kQkMaxVectors = 1 << 20;  // vectors of a chunk: workgroup numbers fit 32 bits
 struct QkFirstTask {
   const uint16_t *x, *fh, *fl;  // input, factor as bf16 hi and lo terms
   float *t;                     // T^T or U
@@ -285,6 +287,7 @@ struct QkFirst {
   QkFirstTask t[kQkTasks];
   int64_t bc;
   int32_t n;
+  uint32_t base;  // first workgroup of the launch (grid_parts)
 };
 struct QkSecondTask {
   const float *p, *q;
@@ -298,6 +301,7 @@ struct QkSecond {
   int64_t bc, D;
   float *out;
   int32_t n, accumulate;
+  uint32_t base;
 };
 struct QkGroup {  // layers of one set of launches; float offsets into the workspace
   int32_t n;
@@ -326,7 +330,7 @@ struct Qk64Dot {  // out[p][q] = sum_k P[p][k] Q[q][k] per vector, rows of K ent
 };
 struct Qk64DotArgs {
   Qk64Dot t[kQk64Tasks];
-  uint32_t blk0[kQk64Tasks];
+  uint32_t blk0[kQk64Tasks], base;
   int64_t nv;
   int32_t n, accumulate;
 };
@@ -340,7 +344,7 @@ struct Qk64Outer {  // out[i][j] = sum_k P(k, i) Q[k][j] (+ theta), P(k, i) = p[
 };
 struct Qk64OuterArgs {
   Qk64Outer t[kQk64Tasks];
-  uint32_t blk0[kQk64Tasks];
+  uint32_t blk0[kQk64Tasks], base;
   int64_t nv;
   int32_t n, out_bf16;
 };

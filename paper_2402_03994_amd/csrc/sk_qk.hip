@@ -87,7 +87,7 @@ union Pack8 {
 template <class Args>
 __device__ __forceinline__ const auto &qk_task(const Args &a) {
   int i = 0;
-  while (i + 1 < a.n && blockIdx.x >= a.t[i + 1].blk0) ++i;
+  while (i + 1 < a.n && a.base + blockIdx.x >= a.t[i + 1].blk0) ++i;
   return a.t[i];
 }
 
@@ -98,7 +98,7 @@ constexpr int kQkBRow = 128 * 2 + 16;     // bytes of one B row chunk in LDS (pa
 template <int NT>
 __global__ __launch_bounds__(256) void k_qk_s1(QkFirst a) {
   const QkFirstTask &task = qk_task(a);
-  const uint32_t blk = blockIdx.x - task.blk0;
+  const uint32_t blk = a.base + blockIdx.x - task.blk0;
   const uint16_t *__restrict__ x = task.x, *__restrict__ B = task.fh, *__restrict__ Blo = task.fl;
   float *__restrict__ tt = task.t;
   const int64_t m = task.m, n = task.n, rows = a.bc * m;
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256) void k_qk_s1(QkFirst a) {
 template <int MT>
 __global__ __launch_bounds__(256) void k_qk_s1a(QkFirst a) {
   const QkFirstTask &task = qk_task(a);
-  const uint32_t blk = blockIdx.x - task.blk0;
+  const uint32_t blk = a.base + blockIdx.x - task.blk0;
   const uint16_t *__restrict__ x = task.x, *__restrict__ Ah = task.fh, *__restrict__ Al = task.fl;
   float *__restrict__ u = task.t;
   const int64_t m = task.m, n = task.n;
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void k_qk_s1a(QkFirst a) {
 template <int MT>
 __global__ __launch_bounds__(256) void k_qk_s1aw(QkFirst a) {
   const QkFirstTask &task = qk_task(a);
-  const uint32_t blk = blockIdx.x - task.blk0;
+  const uint32_t blk = a.base + blockIdx.x - task.blk0;
   const uint16_t *__restrict__ x = task.x, *__restrict__ Ah = task.fh, *__restrict__ Al = task.fl;
   float *__restrict__ u = task.t;
   const int64_t m = task.m, n = task.n;
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256) void k_qk_s2(QkSecond a) {
   const int da = task.da, db = task.db;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nbb = db / (16 * TB), nb = da / (16 * TA) * nbb;
-  uint32_t e0 = blockIdx.x - task.blk0;
+  uint32_t e0 = a.base + blockIdx.x - task.blk0;
   const int blk = (int)(e0 % (uint32_t)nb);
   e0 /= (uint32_t)nb;
   const int64_t v = e0 % (uint32_t)a.bc, z = e0 / (uint32_t)a.bc;
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(256) void k_qk_s2(QkSecond a) {
 __global__ __launch_bounds__(256) void k_qk_s2_sum(QkSecond a) {
   const QkSecondTask &task = qk_task(a);
   const int64_t cnt = (int64_t)task.da * task.db;
-  const int64_t e = (int64_t)(blockIdx.x - task.blk0) * 256 + threadIdx.x;
+  const int64_t e = (int64_t)(a.base + blockIdx.x - task.blk0) * 256 + threadIdx.x;
   if (e >= cnt * a.bc) return;
   float y = 0.0f;
 #pragma unroll 8
@@ -532,24 +532,26 @@ void launch_qk_first(const sk_sketch *s, const QkGroup &g, const void *const *x,
       t.blk0 = (uint32_t)blk;
       blk += !af ? (bc * ld.m + kQkRows - 1) / kQkRows : bc * (ld.nc / (wide ? 512 : 256));
     }
-    if (!a.n) continue;
-    const dim3 grid((unsigned)blk);
-    switch (cls) {
-      case 0: hipLaunchKernelGGL(k_qk_s1<1>, grid, dim3(256), 0, st, a); break;
-      case 1: hipLaunchKernelGGL(k_qk_s1<2>, grid, dim3(256), 0, st, a); break;
-      case 2: hipLaunchKernelGGL(k_qk_s1<3>, grid, dim3(256), 0, st, a); break;
-      case 3: hipLaunchKernelGGL(k_qk_s1<4>, grid, dim3(256), 0, st, a); break;
-      case 4: hipLaunchKernelGGL(k_qk_s1<5>, grid, dim3(256), 0, st, a); break;
-      case 5: hipLaunchKernelGGL(k_qk_s1<6>, grid, dim3(256), 0, st, a); break;
-      case 6: hipLaunchKernelGGL(k_qk_s1<7>, grid, dim3(256), 0, st, a); break;
-      case 7: hipLaunchKernelGGL(k_qk_s1<8>, grid, dim3(256), 0, st, a); break;
-      case 8: hipLaunchKernelGGL(k_qk_s1a<1>, grid, dim3(256), 0, st, a); break;
-      case 9: hipLaunchKernelGGL(k_qk_s1a<2>, grid, dim3(256), 0, st, a); break;
-      case 10: hipLaunchKernelGGL(k_qk_s1a<3>, grid, dim3(256), 0, st, a); break;
-      case 11: hipLaunchKernelGGL(k_qk_s1a<4>, grid, dim3(256), 0, st, a); break;
-      case 12: hipLaunchKernelGGL(k_qk_s1aw<1>, grid, dim3(256), 0, st, a); break;
-      default: hipLaunchKernelGGL(k_qk_s1aw<2>, grid, dim3(256), 0, st, a); break;
-    }
+    grid_parts(blk, [&](uint32_t first, uint32_t count) {
+      const dim3 grid(count);
+      a.base = first;
+      switch (cls) {
+        case 0: hipLaunchKernelGGL(k_qk_s1<1>, grid, dim3(256), 0, st, a); break;
+        case 1: hipLaunchKernelGGL(k_qk_s1<2>, grid, dim3(256), 0, st, a); break;
+        case 2: hipLaunchKernelGGL(k_qk_s1<3>, grid, dim3(256), 0, st, a); break;
+        case 3: hipLaunchKernelGGL(k_qk_s1<4>, grid, dim3(256), 0, st, a); break;
+        case 4: hipLaunchKernelGGL(k_qk_s1<5>, grid, dim3(256), 0, st, a); break;
+        case 5: hipLaunchKernelGGL(k_qk_s1<6>, grid, dim3(256), 0, st, a); break;
+        case 6: hipLaunchKernelGGL(k_qk_s1<7>, grid, dim3(256), 0, st, a); break;
+        case 7: hipLaunchKernelGGL(k_qk_s1<8>, grid, dim3(256), 0, st, a); break;
+        case 8: hipLaunchKernelGGL(k_qk_s1a<1>, grid, dim3(256), 0, st, a); break;
+        case 9: hipLaunchKernelGGL(k_qk_s1a<2>, grid, dim3(256), 0, st, a); break;
+        case 10: hipLaunchKernelGGL(k_qk_s1a<3>, grid, dim3(256), 0, st, a); break;
+        case 11: hipLaunchKernelGGL(k_qk_s1a<4>, grid, dim3(256), 0, st, a); break;
+        case 12: hipLaunchKernelGGL(k_qk_s1aw<1>, grid, dim3(256), 0, st, a); break;
+        default: hipLaunchKernelGGL(k_qk_s1aw<2>, grid, dim3(256), 0, st, a); break;
+      }
+    });
   }
 }
 
@@ -611,21 +613,26 @@ void launch_qk_second(const sk_sketch *s, const QkGroup &g, int64_t b_begin, int
         sblk += (bc * cnt + 255) / 256;
       }
     }
-    if (!a.n) continue;
-    const dim3 grid((unsigned)blk);
-    switch (cls) {
-      case 0: hipLaunchKernelGGL((k_qk_s2<1, 1>), grid, dim3(256), 0, st, a); break;
-      case 1: hipLaunchKernelGGL((k_qk_s2<1, 2>), grid, dim3(256), 0, st, a); break;
-      case 2: hipLaunchKernelGGL((k_qk_s2<1, 4>), grid, dim3(256), 0, st, a); break;
-      case 3: hipLaunchKernelGGL((k_qk_s2<2, 1>), grid, dim3(256), 0, st, a); break;
-      case 4: hipLaunchKernelGGL((k_qk_s2<2, 2>), grid, dim3(256), 0, st, a); break;
-      case 5: hipLaunchKernelGGL((k_qk_s2<2, 4>), grid, dim3(256), 0, st, a); break;
-      case 6: hipLaunchKernelGGL((k_qk_s2<4, 1>), grid, dim3(256), 0, st, a); break;
-      case 7: hipLaunchKernelGGL((k_qk_s2<4, 2>), grid, dim3(256), 0, st, a); break;
-      default: hipLaunchKernelGGL((k_qk_s2<4, 4>), grid, dim3(256), 0, st, a); break;
-    }
+    grid_parts(blk, [&](uint32_t first, uint32_t count) {
+      const dim3 grid(count);
+      a.base = first;
+      switch (cls) {
+        case 0: hipLaunchKernelGGL((k_qk_s2<1, 1>), grid, dim3(256), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((k_qk_s2<1, 2>), grid, dim3(256), 0, st, a); break;
+        case 2: hipLaunchKernelGGL((k_qk_s2<1, 4>), grid, dim3(256), 0, st, a); break;
+        case 3: hipLaunchKernelGGL((k_qk_s2<2, 1>), grid, dim3(256), 0, st, a); break;
+        case 4: hipLaunchKernelGGL((k_qk_s2<2, 2>), grid, dim3(256), 0, st, a); break;
+        case 5: hipLaunchKernelGGL((k_qk_s2<2, 4>), grid, dim3(256), 0, st, a); break;
+        case 6: hipLaunchKernelGGL((k_qk_s2<4, 1>), grid, dim3(256), 0, st, a); break;
+        case 7: hipLaunchKernelGGL((k_qk_s2<4, 2>), grid, dim3(256), 0, st, a); break;
+        default: hipLaunchKernelGGL((k_qk_s2<4, 4>), grid, dim3(256), 0, st, a); break;
+      }
+    });
   }
-  if (sum.n) hipLaunchKernelGGL(k_qk_s2_sum, dim3((unsigned)sblk), dim3(256), 0, st, sum);
+  grid_parts(sblk, [&](uint32_t first, uint32_t count) {
+    sum.base = first;
+    hipLaunchKernelGGL(k_qk_s2_sum, dim3(count), dim3(256), 0, st, sum);
+  });
 }
 
 }  // namespace sk

@@ -195,10 +195,11 @@ __device__ __forceinline__ void qk64_dot(const Qk64Dot &t, int bp, int bq, int k
 template <bool QB>
 __global__ __launch_bounds__(256, 3) void k_qk64_dot(Qk64DotArgs a) {
   __shared__ double red[2][8][4][64];
+  const uint32_t blk = a.base + blockIdx.x;
   int ti = 0;
-  while (ti + 1 < a.n && blockIdx.x >= a.blk0[ti + 1]) ++ti;
+  while (ti + 1 < a.n && blk >= a.blk0[ti + 1]) ++ti;
   const Qk64Dot &t = a.t[ti];
-  uint32_t e = blockIdx.x - a.blk0[ti];
+  uint32_t e = blk - a.blk0[ti];
   const int bp = (int)(e % (uint32_t)t.nbp);
   e /= (uint32_t)t.nbp;
   const int bq = (int)(e % (uint32_t)t.nbq);
@@ -216,11 +217,12 @@ __global__ __launch_bounds__(256, 3) void k_qk64_dot(Qk64DotArgs a) {
 
 // Sums the k ranges' partial products in order, in fp64, into out.
 __global__ __launch_bounds__(256) void k_qk64_sum(Qk64DotArgs a) {
+  const uint32_t blk = a.base + blockIdx.x;
   int ti = 0;
-  while (ti + 1 < a.n && blockIdx.x >= a.blk0[ti + 1]) ++ti;
+  while (ti + 1 < a.n && blk >= a.blk0[ti + 1]) ++ti;
   const Qk64Dot &t = a.t[ti];
   const int64_t cnt = (int64_t)t.np * t.nq;
-  const int64_t e = (int64_t)(blockIdx.x - a.blk0[ti]) * 256 + threadIdx.x;
+  const int64_t e = (int64_t)(blk - a.blk0[ti]) * 256 + threadIdx.x;
   if (e >= cnt * a.nv) return;
   double y = 0.0;
 #pragma unroll 8
@@ -410,10 +412,11 @@ __device__ __forceinline__ void qk64_outer(const Qk64Outer &t, int bm, int64_t b
 template <bool KS, bool QB>
 __global__ __launch_bounds__(256, 3) void k_qk64_outer(Qk64OuterArgs a) {
   __shared__ double red[KS ? 2 : 1][8][4][64];
+  const uint32_t blk = a.base + blockIdx.x;
   int ti = 0;
-  while (ti + 1 < a.n && blockIdx.x >= a.blk0[ti + 1]) ++ti;
+  while (ti + 1 < a.n && blk >= a.blk0[ti + 1]) ++ti;
   const Qk64Outer &t = a.t[ti];
-  const uint32_t e = blockIdx.x - a.blk0[ti], nm = (uint32_t)t.nbm, nn = (uint32_t)t.nbn;
+  const uint32_t e = blk - a.blk0[ti], nm = (uint32_t)t.nbm, nn = (uint32_t)t.nbn;
   const int64_t v = e / (nm * nn);
   const uint32_t r = e % (nm * nn);
   // KS: the row blocks of one column block (the same input) next to each other
@@ -438,6 +441,9 @@ namespace {
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Workgroup numbers of a group stay below 2^32 (a call's chunks have at most 2^20 vectors, and a workgroup writes 64
+// bytes or more of a matrix of more than one), but not its threads: a one-row or one-column matrix makes a workgroup of
+// every 64 or 32 values, and nine of 2^19 entries with 256 vectors are 2^32 threads.
 void launch_dot(Qk64DotArgs &a, bool qb, hipStream_t st) {
   int64_t blk = 0;
   for (int i = 0; i < a.n; ++i) {
@@ -448,11 +454,13 @@ void launch_dot(Qk64DotArgs &a, bool qb, hipStream_t st) {
     a.blk0[i] = (uint32_t)blk;
     blk += (int64_t)t.nbp * t.nbq * t.nk * a.nv;
   }
-  if (!a.n) return;
-  if (qb)
-    hipLaunchKernelGGL(k_qk64_dot<true>, dim3((unsigned)blk), dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL(k_qk64_dot<false>, dim3((unsigned)blk), dim3(256), 0, st, a);
+  grid_parts(blk, [&](uint32_t first, uint32_t count) {
+    a.base = first;
+    if (qb)
+      hipLaunchKernelGGL(k_qk64_dot<true>, dim3(count), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL(k_qk64_dot<false>, dim3(count), dim3(256), 0, st, a);
+  });
 }
 
 template <bool KS>
@@ -466,11 +474,13 @@ void launch_outer(Qk64OuterArgs &a, bool qb, hipStream_t st) {
     a.blk0[i] = (uint32_t)blk;
     blk += (int64_t)t.nbn * t.nbm * a.nv;
   }
-  if (!a.n) return;
-  if (qb)
-    hipLaunchKernelGGL((k_qk64_outer<KS, true>), dim3((unsigned)blk), dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_qk64_outer<KS, false>), dim3((unsigned)blk), dim3(256), 0, st, a);
+  grid_parts(blk, [&](uint32_t first, uint32_t count) {
+    a.base = first;
+    if (qb)
+      hipLaunchKernelGGL((k_qk64_outer<KS, true>), dim3(count), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL((k_qk64_outer<KS, false>), dim3(count), dim3(256), 0, st, a);
+  });
 }
 
 }  // namespace
@@ -594,7 +604,10 @@ void launch_qk64_second(const sk_sketch *s, const Qk64Group &g, int64_t b_begin,
     }
   }
   launch_dot(d, false, st);
-  if (r.n) hipLaunchKernelGGL(k_qk64_sum, dim3((unsigned)blk), dim3(256), 0, st, r);
+  grid_parts(blk, [&](uint32_t first, uint32_t count) {
+    r.base = first;
+    hipLaunchKernelGGL(k_qk64_sum, dim3(count), dim3(256), 0, st, r);
+  });
 }
 
 Qk64Group qk64_group_T(const sk_sketch *s, int l0, int count, int64_t bc, int64_t ws_bytes) {

@@ -50,3 +50,19 @@ def test_qk_fp64_sums(name, batch, ws_mb, dtype, dev, monkeypatch):  # noqa: F81
     for o, r in zip(outs, refs):
         assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL)
     s.close()
+
+
+# 18.9 million workgroups of 64 outputs (more than one launch takes): every vector is the first one times a power of two
+def test_qk_thin_transpose(dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    shapes, batch, seed = [(1, 2 ** 19, 1, 1)] * 9, 256, 6
+    s = Sketch("qk", shapes, 9, seed, device=dev)
+    g = torch.Generator().manual_seed(seed)
+    z0 = torch.randn((1, 9), generator=g)
+    p2 = 2.0 ** (torch.arange(batch) % 7)
+    outs = s.apply_T((z0 * p2[:, None]).contiguous().to(dev))
+    refs = O.apply_T("qk", shapes, 9, seed, z0.numpy().astype(np.float64))
+    for o, r in zip(outs, refs):
+        assert rel_err(o[:1].cpu().numpy(), r) < TOL
+        assert torch.equal(o, o[:1] * p2.to(dev)[:, None])
+    s.close()
