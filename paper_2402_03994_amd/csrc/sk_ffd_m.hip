@@ -162,12 +162,10 @@ __global__ __launch_bounds__(256, SRC == kRowsFwd ? 3 : 4) void k_ffdM_rows(cons
       const float *z = (const float *)src + (b_begin + v) * D + i0 + col;
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
-        const float4 u = *reinterpret_cast<const float4 *>(z + r * 1024);
+        const f4u u = *reinterpret_cast<const f4u *>(z + r * 1024);  // z may start at any element
         const uint32_t bits = sgn[r * 32 + (col >> 5)] >> (col & 31);
-        e[r][0] = flip(u.x, bits & 1u);
-        e[r][1] = flip(u.y, (bits >> 1) & 1u);
-        e[r][2] = flip(u.z, (bits >> 2) & 1u);
-        e[r][3] = flip(u.w, (bits >> 3) & 1u);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e[r][q] = flip(u[q], (bits >> q) & 1u);
       }
     } else {
       const float *blk = (const float *)src + (v * nblk + b) * D;
