@@ -433,6 +433,9 @@ __global__ __launch_bounds__(256) void k_afjl_fold1(const FoldItem *__restrict__
   }
 }
 
+// The register tails read a layer's fold partials through a buffer resource, below 2^31 bytes.
+static bool tail_parts_ok(int64_t parts, int64_t bc, int Lw) { return parts * bc * Lw * 4 < (1ll << 31); }
+
 // Workgroups per fold item: the fold's grid is brought to at most 1024
 // workgroups (four per CU, what the kernels' LDS allows) while every share
 // keeps 8 or more rows; partial sums beyond the workspace and the tails for
@@ -448,18 +451,21 @@ int afjl_fold_split(const sk_sketch *s, int l0, int l1, int esz, int64_t bc, int
   if (s->R > 64) return 1;
   const int64_t items = s->layers[l1 - 1].item_off + s->layers[l1 - 1].n_items - s->layers[l0].item_off;
   int64_t most = 0, n = 0;  // rows of the longest item, entries of a vector
+  int64_t layer_items = 0;  // of the layer with the most
   for (int l = l0; l < l1; ++l) {
     const LayerDesc &ld = s->layers[l];
     const int64_t t = s->R == 1 ? ld.rows_live : (ld.rows_live + ld.dk1 - 1) / ld.dk1 * (ld.dk1 / s->R);
     most = std::max(most, std::min<int64_t>(t, kFoldRowsPerItem));
     n += ld.n;
+    layer_items = std::max<int64_t>(layer_items, ld.n_items);
   }
   const int64_t launches = (l1 - l0 + kMaxPtrs - 1) / kMaxPtrs;
   const bool r64 = s->R == 64;
   if (items * rows >= launches * (r64 ? 2048 : 3072) && (r64 || n * rows * esz >= launches << 30)) return 1;
   const int64_t blocks = items * (rows == 1 ? 1 : (rows + 7) / 8), least = r64 ? 16 : 8;
   int S = 1;
-  while (blocks * S * 2 <= 1024 && most >= least * S * 2 &&
+  // (layers whose partials exceed a buffer resource go through a tail that knows no shares)
+  while (blocks * S * 2 <= 1024 && most >= least * S * 2 && tail_parts_ok(layer_items * S * 2, bc, s->Lw) &&
          bc * (items * S * 2 * s->Lw + (int64_t)kTailGroups * s->D) * 4 <= s->ws_bytes)
     S *= 2;
   return S;
@@ -791,10 +797,9 @@ static int tail_groups(const sk_sketch *s, int l_begin, int l_end, int G, TailGr
 
 void launch_afjl_tail(const sk_sketch *s, int l_begin, int l_end, int item_begin, int split, const float *part,
                       int64_t bc, int64_t b_begin, int64_t batch, float *out, bool accumulate, hipStream_t st) {
-  // the register tails read each layer's partials through a buffer resource
-  bool small_parts = true;
+  bool small_parts = true;  // always where items are split (afjl_fold_split)
   for (int l = l_begin; l < l_end; ++l)
-    small_parts = small_parts && (int64_t)s->layers[l].n_items * split * bc * s->Lw * 4 < (1ll << 31);
+    small_parts = small_parts && tail_parts_ok((int64_t)s->layers[l].n_items * split, bc, s->Lw);
   if (s->R >= 128 && s->Lw == 1024 && small_parts) {
     const int64_t rows = (batch - b_begin) < bc ? (batch - b_begin) : bc;
     // layer groups until the workgroups (32 per vector and group) fill the CUs, 1024 / R each by LDS
