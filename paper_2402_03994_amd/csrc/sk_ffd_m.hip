@@ -3,7 +3,10 @@
 // A block's coordinates are i = (r, c), r < R = D / 1024, c < 1024, and
 // H_D = H_R (x) H_1024: a row kernel transforms 8 rows of 1024 in LDS, a column
 // kernel a tile of 2^lgcs columns by R rows.  Four passes per direction over
-// the live blocks (unnormalised transforms, 1/D applied at the end):
+// the live blocks; g carries 1/D (a power of two) for both unnormalised
+// transforms, so that intermediates stay within sqrt(D) of the input either way.
+// Normalised row passes would keep them closer, but cost 2 us of 42 to 86 each
+// (153 blocks of 2^16, 4 vectors):
 //   forward     rows(x) -> columns, times g -> rows gathered through
 //               pi_b^{-1} -> columns, signs, summed over a run of blocks
 //   transpose   rows(B_b z) -> columns -> rows gathered through pi_b, times g
@@ -28,19 +31,14 @@ namespace sk {
 
 namespace {
 
-// Workgroup -> (block b, part t of T): the T parts of each of the first
+// Workgroup -> (block b, part t of 2^lgT): the parts of each of the first
 // `local` blocks (a multiple of 8) on one XCD, those of the others in a row.
 // False past the last block.
-__device__ __forceinline__ bool place(uint32_t id, uint32_t T, int64_t nblk, int64_t local, int64_t &b, int &t) {
-  if (id >= (uint32_t)local * T) {
-    const uint32_t e = id - (uint32_t)local * T;
-    b = local + e / T;
-    t = (int)(e % T);
-    return b < nblk;
-  }
-  const uint32_t q = id >> 3;
-  b = (int64_t)(q / T) * 8 + (id & 7);
-  t = (int)(q % T);
+__device__ __forceinline__ bool place(uint32_t id, int lgT, int64_t nblk, int64_t local, int64_t &b, int &t) {
+  const bool spread = id >= (uint32_t)local << lgT;
+  const uint32_t q = spread ? id - ((uint32_t)local << lgT) : id >> 3;
+  b = spread ? local + (q >> lgT) : (int64_t)(q >> lgT) * 8 + (id & 7);
+  t = (int)(q & ((1u << lgT) - 1));
   return b < nblk;
 }
 
@@ -91,7 +89,7 @@ enum { kRowsX = 0, kRowsZ = 1, kRowsInv = 2, kRowsFwd = 3 };
 //   kRowsX    x of the layer (zero past its end)
 //   kRowsZ    B_b z
 //   kRowsInv  src gathered through pi_b^{-1}
-//   kRowsFwd  g . (src gathered through pi_b)
+//   kRowsFwd  g / D . (src gathered through pi_b)
 template <int SRC, bool BF16>
 __global__ __launch_bounds__(256, SRC == kRowsFwd ? 3 : 4) void k_ffdM_rows(const LayerDesc *__restrict__ layers, int layer,
                                                    const void *__restrict__ src, int lgD, int64_t nblk,
@@ -105,7 +103,7 @@ __global__ __launch_bounds__(256, SRC == kRowsFwd ? 3 : 4) void k_ffdM_rows(cons
   const LayerDesc &ld = layers[layer];
   int64_t b;
   int t;
-  if (!place(blockIdx.x, 1u << (lgD - 13), nblk, local, b, t)) return;  // uniform
+  if (!place(blockIdx.x, lgD - 13, nblk, local, b, t)) return;  // uniform
   const int64_t D = 1ll << lgD;
   const int col = 4 * threadIdx.x;
   const int i0 = t * 8192;  // first coordinate of the rows, within the block
@@ -124,9 +122,13 @@ __global__ __launch_bounds__(256, SRC == kRowsFwd ? 3 : 4) void k_ffdM_rows(cons
     __syncthreads();  // the tables make room for the rows
   }
   if (SRC == kRowsFwd) {
+    const float gs = 1.0f / (float)(1 << lgD);
 #pragma unroll
-    for (int r = 0; r < 8; ++r)
+    for (int r = 0; r < 8; ++r) {
       gauss4((uint64_t)(b * D + i0 + r * 1024 + col) >> 2, (uint32_t)ld.layer_id, ST_GAUSS, key, g[r]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) g[r][q] *= gs;
+    }
   }
   if (SRC == kRowsZ) {
     if (threadIdx.x < 64) {  // one Philox block per 128 coordinates
@@ -233,7 +235,7 @@ struct Tile {
 };
 }  // namespace
 
-// In place: H_R along the rows, times g (forward).
+// In place: H_R along the rows, times g / D (forward).
 template <int LGD, bool G>
 __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_cols(const LayerDesc *__restrict__ layers, int layer,
                                                                    int64_t nblk, int64_t local, int64_t bc,
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_cols(const LayerDe
   const LayerDesc &ld = layers[layer];
   int64_t b;
   int t;
-  if (!place(blockIdx.x, T::TILES, nblk, local, b, t)) return;
+  if (!place(blockIdx.x, 10 - T::LGCS, nblk, local, b, t)) return;
   const int c0 = t << T::LGCS;
   float x[T::NE];
   int64_t v = blockIdx.y;
@@ -252,7 +254,11 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_cols(const LayerDe
   if (G) {
     const uint64_t q0 = ((uint64_t)(b << LGD) + (uint64_t)(T::place4() + c0)) >> 2;
 #pragma unroll
-    for (int i = 0; i < T::NG; ++i) gauss4(q0 + T::off4(i) / 4, (uint32_t)ld.layer_id, ST_GAUSS, key, gg[i]);
+    for (int i = 0; i < T::NG; ++i) {
+      gauss4(q0 + T::off4(i) / 4, (uint32_t)ld.layer_id, ST_GAUSS, key, gg[i]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) gg[i][q] *= 1.0f / (float)(1 << LGD);
+    }
   }
   for (;;) {
     T::stage(s, x);
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_cols(const LayerDe
   }
 }
 
-// Transpose, last pass: H_R, 1/D, theta0, the layer's outputs.
+// Transpose, last pass: H_R, theta0, the layer's outputs.
 template <int LGD>
 __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_out(const LayerDesc *__restrict__ layers, int layer,
                                                                   int64_t nblk, int64_t local, int64_t b_begin,
@@ -286,11 +292,10 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_out(const LayerDes
   const int64_t n = layers[layer].n;
   int64_t b;
   int t;
-  if (!place(blockIdx.x, T::TILES, nblk, local, b, t)) return;
+  if (!place(blockIdx.x, 10 - T::LGCS, nblk, local, b, t)) return;
   const int64_t j0 = b << LGD;
   const int lim = (int)(n - j0 < (1ll << LGD) ? n - j0 : 1ll << LGD);  // entries of the block
   const int i0 = T::place1() + (t << T::LGCS);
-  constexpr float inv = 1.0f / (float)(1 << LGD);
   // a whole block takes scalar offsets; the last one compares every entry with its end
   const bool full = lim == 1 << LGD;
   float x[T::NE], th[T::NE];
@@ -308,17 +313,17 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_out(const LayerDes
 #pragma unroll 1
       for (int i = 0; i < T::NE; ++i) {
         const int k = i0 + T::off1(i);
-        if (k < lim) store_out(out, out_dtype, o0 + k, d[272 * i] * inv + (theta0 ? theta0[j0 + k] : 0.0f));
+        if (k < lim) store_out(out, out_dtype, o0 + k, d[272 * i] + (theta0 ? theta0[j0 + k] : 0.0f));
       }
     } else if (out_dtype == SK_BF16) {
       uint16_t *o = (uint16_t *)out + o0;
 #pragma unroll
-      for (int i = 0; i < T::NE; ++i) (o + T::off1(i))[i0] = f32_to_bf16(d[272 * i] * inv + th[i]);
+      for (int i = 0; i < T::NE; ++i) (o + T::off1(i))[i0] = f32_to_bf16(d[272 * i] + th[i]);
     } else {
       const __amdgpu_buffer_rsrc_t r = buf_rsrc((float *)out + o0, 4u << LGD);
 #pragma unroll
       for (int i = 0; i < T::NE; ++i)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(d[272 * i] * inv + th[i]), r, i0 * 4, T::off1(i) * 4, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(d[272 * i] + th[i]), r, i0 * 4, T::off1(i) * 4, 0);
     }
     v += gridDim.y;
     if (v >= bc) return;
@@ -328,7 +333,7 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_out(const LayerDes
 }
 
 // Forward, last pass: H_R and the signs of the blocks of run blockIdx.z, summed
-// in registers in block order, to part[run][v][D] (1/D applied).  gridDim.x =
+// in registers in block order, to part[run][v][D].  gridDim.x =
 // tiles: a run's tile stays on one workgroup, its next block in flight.
 template <int LGD>
 __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_sum(const LayerDesc *__restrict__ layers, int layer,
@@ -369,10 +374,9 @@ __global__ __launch_bounds__(256, Tile<LGD>::OCC) void k_ffdM_sum(const LayerDes
     }
     __syncthreads();
   }
-  constexpr float inv = 1.0f / (float)(1 << LGD);
   float *o = part + (((int64_t)blockIdx.z * bc + v) << LGD) + T::place1() + c0;
 #pragma unroll
-  for (int i = 0; i < T::NE; ++i) o[T::off1(i)] = acc[i] * inv;
+  for (int i = 0; i < T::NE; ++i) o[T::off1(i)] = acc[i];
 }
 
 namespace {

@@ -65,3 +65,19 @@ def parity(lgD, shapes, batch, seed, dtype, dev):  # noqa: F811
 @pytest.mark.parametrize("lgD,blocks,batch", [(19, 1, 1), (18, 2, 3), (17, 9, 4), (15, 12, 16), (17, 5, 5), (16, 15, 8)])
 def test_ffd_mid_few_blocks(lgD, blocks, batch, dev):  # noqa: F811
     parity(lgD, [(1, (blocks << lgD) - 1021)], batch, 800 + lgD + blocks, "f32", dev)
+
+
+# No intermediate may overflow where inputs and results are far from the end of the type: 2^112 times the vectors gives
+# 2^112 times the results, bit for bit (an unnormalised pair of transforms grows by D).
+@pytest.mark.parametrize("lgD", [14, 16, 17, 19])
+def test_ffd_mid_large_values(lgD, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    D = 1 << lgD
+    s = Sketch("ffd", [(1, 2 * D - 3)], D, 19, device=dev)
+    x = rand_inputs([(1, 2 * D - 3)], 2, 19)[0].to(dev)
+    y = s.apply([x])
+    assert torch.isfinite(y).all() and torch.equal(s.apply([x * 2.0 ** 112]), y * 2.0 ** 112)
+    z = torch.randn((2, D), generator=torch.Generator().manual_seed(20)).to(dev)
+    o = s.apply_T(z)[0]
+    assert torch.isfinite(o).all() and torch.equal(s.apply_T(z * 2.0 ** 112)[0], o * 2.0 ** 112)
+    s.close()
