@@ -32,6 +32,11 @@
 
 namespace sk {
 
+// The four transforms of a layer are unnormalised, sqrt(N' D) in all: 2^-10 of
+// it goes in between the first two and the last two, so that intermediates stay
+// near the input's size (powers of two: the same bits).
+constexpr float kMidScale = 1.0f / 1024.0f;
+
 // ---- A ---------------------------------------------------------------------
 // Workgroup per 8 rows a, vector and layer: thread (i = tid / 32, c = tid % 32)
 // reads columns c + 32 k of row i through pi2_l^{-1} (4 KB of z, in L1).
@@ -117,7 +122,7 @@ __global__ __launch_bounds__(1024) void k_affdTT_cols(const LayerDesc *__restric
   for (int k = 0; k < 32; ++k) high[33 * k] = u[k];
   __syncthreads();
 #pragma unroll
-  for (int m = 0; m < 32; ++m) u[m] = low[m];
+  for (int m = 0; m < 32; ++m) u[m] = low[m] * kMidScale;
   fwht_regs_t<32>(u);
   for (int t = t0; t < t1; ++t) {
     __syncthreads();  // the block's last readers are done
@@ -162,8 +167,11 @@ __device__ __forceinline__ void affd_tile_gauss(const LayerDesc &ld, int lgcs, i
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
     const int e = 4 * threadIdx.x + 1024 * i;  // lgcs >= 5: four columns of one row
-    if (e < tot)
+    if (e < tot) {
       gauss4((uint64_t)((e >> lgcs) * 1024 + c0 + (e & cmask)) >> 2, (uint32_t)ld.layer_id, ST_GAUSS, key, gg[i]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) gg[i][q] *= kMidScale;
+    }
   }
 }
 // H_p, g, H_p on the filled tile (rows above bit lgcs); starts and ends synchronised.
@@ -435,7 +443,7 @@ __global__ __launch_bounds__(1024) void k_affdF_cols(const LayerDesc *__restrict
   }
   fwht_regs_t<32>(f);
 #pragma unroll
-  for (int m = 0; m < 32; ++m) low[m] = f[m];  // the places this thread has just read
+  for (int m = 0; m < 32; ++m) low[m] = f[m] * kMidScale;  // the places this thread has just read
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < 32; ++k) f[k] = high[33 * k];
@@ -519,7 +527,7 @@ AffdTTGroup affd_T_group(const sk_sketch *s, int l0, int l1, int64_t bc, void *c
     g.m[g.n] = affd_transposed_path(s, l0 + g.n) ? s->d_mtab + s->mtab_off[l0 + g.n] : nullptr;
     g.out[g.n] = out[g.n];
     g.th[g.n] = theta0 ? (const float *)theta0[g.n] : nullptr;
-    g.scale[g.n] = (float)(1.0 / std::sqrt((double)ld.np * (double)s->D));
+    g.scale[g.n] = (float)(1.0 / std::sqrt((double)ld.np * (double)s->D)) / kMidScale;
     ++g.n;
   }
   return g;
@@ -619,7 +627,7 @@ AffdTTGroup affd_F_group(const sk_sketch *s, const int *layers, int count, int l
       g.t0[g.n] = r * g.spw;
       g.m[g.n] = big ? s->d_mtab + s->mtab_off[l] : nullptr;
       g.out[g.n] = const_cast<void *>(x[l - l0]);
-      g.scale[g.n] = (float)(1.0 / std::sqrt((double)ld.np * (double)s->D));
+      g.scale[g.n] = (float)(1.0 / std::sqrt((double)ld.np * (double)s->D)) / kMidScale;
       g.u_off[g.n] = g.n * bc * s->D;
       ++g.n;
     }

@@ -60,3 +60,20 @@ def test_affd_few_vectors(case, batch, dtype, dev, monkeypatch):  # noqa: F811
     s.apply(xd, out=y, accumulate=True)
     assert rel_err(y.cpu().numpy(), 2 * ref) < TOL_F32
     s.close()
+
+
+# Intermediates stay near the input's size: 2^112 times z and 2^108 times the vectors (the sum over several slabs adds
+# their number) give as many times the results, bit for bit; four unnormalised transforms grow by sqrt(N' D), 2^11 to
+# 2^20 here.
+@pytest.mark.parametrize("D,shapes", [(16384, [(1, 2 ** 17 + 3), (1, 768), (1, 2 ** 19 - 5), (1, 3 * 2 ** 20 + 1)]),
+                                      (1 << 17, [(1, 2 ** 19), (1, 2 ** 20 + 7)]), (2048, [(1, 3), (33, 1023)])])
+def test_affd_large_values(D, shapes, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    s = Sketch("affd", shapes, D, 27, device=dev)
+    z = torch.randn((5, D), generator=torch.Generator().manual_seed(28)).to(dev)
+    for a, b in zip(s.apply_T(z * 2.0 ** 112), s.apply_T(z)):
+        assert torch.isfinite(b).all() and torch.equal(a, b * 2.0 ** 112)
+    xs = [x.to(dev) for x in rand_inputs(shapes, 2, 29)]
+    y = s.apply(xs)
+    assert torch.isfinite(y).all() and torch.equal(s.apply([x * 2.0 ** 108 for x in xs]), y * 2.0 ** 108)
+    s.close()
