@@ -90,7 +90,8 @@ enum {
   SK_OK = 0,
   SK_EINVAL = -1,      /* bad argument: kind, D, shapes, null pointer, batch  */
   SK_EDTYPE = -2,      /* unknown dtype                                       */
-  SK_ENOMEM = -3,      /* device allocation failed at creation                */
+  SK_ENOMEM = -3,      /* an allocation failed: of the device at creation, of
+                          the host's layer lists in sketch_apply              */
   SK_EHIP = -4,        /* a HIP runtime call failed                           */
   SK_EUNSUPPORTED = -5 /* valid in the math but outside what the kernels take */
 };

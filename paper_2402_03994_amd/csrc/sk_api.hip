@@ -703,7 +703,7 @@ static int check_range(const sk_sketch *s, int32_t first_layer, int32_t n_layers
 }
 
 int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t batch, float *out,
-                 int32_t first_layer, int32_t n_layers, int32_t accumulate, void *stream) {
+                 int32_t first_layer, int32_t n_layers, int32_t accumulate, void *stream) try {
   if (!s) return fail(SK_EINVAL, "sketch is NULL");
   if (dtype != SK_F32 && dtype != SK_BF16) return fail(SK_EDTYPE, "dtype must be SK_F32 or SK_BF16");
   if (batch < 0) return fail(SK_EINVAL, "batch must be >= 0");
@@ -1066,6 +1066,9 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SK_EHIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
   return SK_OK;
+} catch (const std::bad_alloc &) {  // the layer lists; no exception leaves the C entry
+  g_err = "out of memory";  // fits the string without an allocation
+  return SK_ENOMEM;
 }
 
 // Allocation-free forward sketch: sketch_apply with the per-call scratch in
