@@ -77,3 +77,47 @@ def test_affd_large_values(D, shapes, dev):  # noqa: F811
     y = s.apply(xs)
     assert torch.isfinite(y).all() and torch.equal(s.apply([x * 2.0 ** 108 for x in xs]), y * 2.0 ** 108)
     s.close()
+
+
+# Calls of 4 to 32 vectors: one-slab layers in the grouped passes first, then the several-slab layers and the small ones
+# through their own, all in one output; 33 vectors leave the grouped passes.  The small workspace holds some of the
+# layers' groups and few slots of G^T.
+MIXED = [(1, 768), (33, 1023), (1, 2 ** 17 + 3), (1, 2 ** 19 - 5), (1, 2 ** 20 + 5), (3, 1000), (1, 3 * 2 ** 18 + 1), (1, 100)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,batch,ws_mb", [(16384, 4, None), (16384, 8, 48), (4096, 32, None), (2048, 33, None),
+                                           (65536, 8, None), (65536, 5, 40), (16384, 32, 96)])
+def test_affd_mixed_paths(D, batch, ws_mb, dtype, dev, monkeypatch):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    if ws_mb is not None:
+        monkeypatch.setenv("SK_WORKSPACE_MB", str(ws_mb))
+    seed = 970 + batch
+    s = Sketch("affd", MIXED, D, seed, device=dev)
+    xs = rand_inputs(MIXED, batch, seed, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ref = O.apply("affd", MIXED, D, seed, [oracle_in(x)[0] for x in xs], dtype=dtype)
+    xd = [x.to(dev) for x in xs]
+    y = s.apply(xd)
+    assert rel_err(y.cpu().numpy(), ref) < TOL_F32
+    s.apply(xd, out=y, accumulate=True)
+    assert rel_err(y.cpu().numpy(), 2 * ref) < TOL_F32
+    s.close()
+
+
+# One-slab column tiles over more vectors than 2048 workgroups take at once: a workgroup goes on to further vectors.
+# 40 layers of 512 rows make 1280 tiles, each with all three vectors on one workgroup; 40 of 64 rows make 640 of the
+# smaller tiles, eight vectors on three workgroups each.
+@pytest.mark.parametrize("n,batch", [(2 ** 19 - 77, 3), (2 ** 16 - 5, 8)])
+def test_affd_vector_turns(n, batch, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    shapes, D, seed = [(1, n - 13 * i) for i in range(40)], 2048, 33
+    s = Sketch("affd", shapes, D, seed, device=dev)
+    xs = rand_inputs(shapes, batch, seed)
+    y = s.apply([x.to(dev) for x in xs])
+    assert rel_err(y.cpu().numpy(), O.apply("affd", shapes, D, seed, [x.numpy() for x in xs])) < TOL_F32
+    z = torch.randn((batch, D), generator=torch.Generator().manual_seed(seed))
+    outs = s.apply_T(z.to(dev))
+    refs = O.apply_T("affd", shapes, D, seed, z.numpy().astype(np.float64))
+    for o, r in zip(outs, refs):
+        assert rel_err(o.cpu().numpy(), r) < TOL_F32
+    s.close()

@@ -81,3 +81,12 @@ def test_ffd_mid_large_values(lgD, dev):  # noqa: F811
     o = s.apply_T(z)[0]
     assert torch.isfinite(o).all() and torch.equal(s.apply_T(z * 2.0 ** 112)[0], o * 2.0 ** 112)
     s.close()
+
+
+# More blocks than workgroups are wanted for: a workgroup goes on to a second and third vector (every gridDim.y-th), in
+# the row, column and output passes, the column tiles of 2^13 and 2^14 values, whole blocks and a ragged last one
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("lgD,blocks,batch", [(14, 1025, 3), (16, 137, 4), (19, 17, 5)])
+def test_ffd_mid_vector_turns(lgD, blocks, batch, dtype, dev):  # noqa: F811
+    # row passes 2064, 1152 and 1088 workgroups per vector, column passes 2064, 1152 and 544, of 2048 in all
+    parity(lgD, [(1, (blocks << lgD) - 4099)], batch, 900 + lgD, dtype, dev)
