@@ -722,11 +722,11 @@ __global__ __launch_bounds__(256, 4) void k_afjl_tail_reg(const LayerDesc *__res
 // H_{R/32} (x) H_32 with one LDS transpose (128 R bytes).  A group's sum goes
 // to slot gi of dst (one group: straight to the output).
 // R < 1024 went through LDS passes over a 4096-value tile, every partial and G
-// load waited for, one workgroup per tile walking all layers: 1920 us of an S
-// H S^T of 8 GPT-2 blocks (one vector, D = 2^18), 2490 -> 579 us as a whole.
-// 4 blocks of width 500 forward, 1 / 8 / 32 vectors: 926 / 933 / 3475 -> 66 /
-// 202 / 808 us at D = 2^18.  R = 1024 had one group: a 2048-wide decoder block
-// of one vector 136 -> 90 us, 8 vectors (256 workgroups) alike.
+// load waited for, one workgroup per tile walking all layers: an S H S^T of 8
+// GPT-2 blocks (one vector, D = 2^18) 2442 -> 517 us as a whole.  4 blocks of
+// width 500 forward, 1 / 8 / 32 vectors: 886 / 881 / 3223 -> 64 / 178 / 707 us at
+// D = 2^18.  R = 1024 had one group: the matrices of a 2048-wide decoder block,
+// one vector, 114 -> 86 us, 8 vectors (256 workgroups) alike.
 template <int R>
 __global__ __launch_bounds__(R) void k_afjl_tail_wide(const LayerDesc *__restrict__ layers,
                                                       const int2 *__restrict__ rslot,

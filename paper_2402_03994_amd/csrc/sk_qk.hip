@@ -80,9 +80,9 @@ union Pack8 {
 // Layers of a launch are tasks in the kernel arguments: one layer's contraction
 // leaves the chip idle up to some 30 vectors (48 workgroups for a 768 x 768
 // matrix and 16 vectors, and 45 us a layer whatever the batch).  12 GPT-2
-// blocks (60 matrices), one launch per layer and contraction against groups:
-// 2674 -> 591 us for 8 vectors, 3145 -> 1844 for 32; a 2048-wide decoder block,
-// 64 vectors: 1542 -> 1447.  Dividing one layer's contraction index instead
+// blocks (72 matrices), one launch per layer and contraction against groups:
+// 3355 -> 594 us for 8 vectors, 3620 -> 1849 for 32; a 2048-wide decoder block,
+// 64 vectors: 1628 -> 1452.  Dividing the first contraction's index instead
 // writes more partial products than it reads inputs (3741 for the 32).
 template <class Args>
 __device__ __forceinline__ const auto &qk_task(const Args &a) {
@@ -491,8 +491,8 @@ bool qk_bf16_path(const LayerDesc &ld, int dtype, int64_t batch) {
 }
 
 // First products held by a group: half of the memory-side cache, so that the second contraction finds them there.
-// A layer that fills the chip alone needs no group: 145 matrices of a 2048-wide decoder, 256 vectors, took
-// 154 to 160 ms in groups of up to 32 (33 to 268 MB of first products each), 156.5 layer by layer, 152.6 so.
+// A layer that fills the chip alone needs no group: 145 matrices of a 2048-wide decoder, 256 vectors (33 to 268 MB of
+// first products per matrix), took 154 to 160 ms in groups of up to 32, 156.5 layer by layer, 152.6 so.
 constexpr int64_t kQkGroupBytes = 128ll << 20;
 
 QkGroup qk_group(const sk_sketch *s, const int *layers, int count, int64_t bc, int64_t ws_bytes) {
