@@ -498,19 +498,43 @@ bool affd_T_grouped(const sk_sketch *s, int layer) {
   return s->D > 1024 && ld.K == 2 && ld.L == 1024 && ld.dk1 >= 2 && ld.dk1 < 1024;
 }
 
-// One vector of three GPT-2 blocks (D = 2^14): 487 us by the other paths, 184
-// here; three vectors 546 -> 396, four 570 -> 493, six 669 -> 684: a layer of
-// several slabs goes here up to three vectors, above which the 8 vectors that
-// share each M row there count (all of GPT-2 small, D = 2^16: 2221 -> 875 us
-// for one vector, 2650 -> 2043 for three, 2510 against 2618 for four).  Layers
-// of one slab of fewer than 1024 rows (five launches each, there) gain at every
+// Live slabs of a layer.
+static int64_t affd_slabs(const LayerDesc &ld) { return (ld.rows_live + ld.dk1 - 1) / ld.dk1; }
+
+// Forward, layers of one slab of fewer than 1024 rows (five launches each on the other paths) gain here at every
 // size measured (widths 300 to 420, D = 2^12 to 2^17): 627 -> 117 us for one
 // vector, 863 -> 419 for 8, 1343 -> 1175 for 16, 1853 -> 1776 and 2258 -> 2268
 // for 32.  Biases (N' = D, at most 8 rows) keep their own kernels from four
 // vectors on (D = 2^14, 8 vectors: 55 against 70 us).
-bool affd_F_grouped(const sk_sketch *s, int layer, int64_t bc) {
+// Layers of 1024-row slabs, up to three vectors, gain the launches that they
+// share (some 40 us each), and lose that every vector reads M for itself (there
+// 8 vectors share a row) and writes a sum of D values per four slabs: by the
+// slopes of 1 to 9 layers some 3 us for each slab of every further vector (0.5 of
+// the first), 11.5 for each such sum at D = 2^20; the rule is in halves of a us,
+// its bounds where calls of GPT-2-like blocks and of equal matrices break even.  9 matrices, other path / here: D = 2^17, of 4
+// slabs, one / two / three vectors 489 / 279, 539 / 502, 590 / 597; of 7, 537 /
+// 370, 614 / 596, 689 / 802; of 16, three, 1298 / 1779; D = 2^20, of 4, one / two
+// 509 / 374, 509 / 599; of 16, one, 927 / 1075.  With many layers the sums of the other path take
+// several passes (48 matrices of one slab, D = 2^20, three vectors: 2198 / 2035,
+// 9 of them 404 / 436).  A lone layer shares nothing, and of several slabs it has
+// 32 workgroups per four of them (4096 x 1024, D = 2^17, one vector: 69 / 80; 1024
+// x 1024, D = 2^17, 53 / 43, D = 2^20 61 / 66).
+static bool affd_F_grouped(const sk_sketch *s, int layer, int64_t bc, int n) {
   if (!affd_T_grouped(s, layer)) return false;
-  return bc <= 3 || (bc <= 32 && !affd_transposed_path(s, layer) && !affd_small_path(s, layer));
+  if (!affd_transposed_path(s, layer)) return bc <= 3 || (bc <= 32 && !affd_small_path(s, layer));
+  const LayerDesc &ld = s->layers[layer];
+  const int64_t slabs = (ld.rows_live + ld.dk1 - 1) / ld.dk1, sums = (slabs + 3) / 4;
+  if (n == 1) return slabs == 1 && bc <= 3 && bc * s->D < 1 << 20;
+  return bc <= 3 && slabs * (6 * bc - 5) + 23 * bc * sums * s->D / (1 << 20) < (bc == 1 ? 90 : n >= 16 ? 84 : 74);
+}
+
+std::vector<int> affd_F_layers(const sk_sketch *s, int l0, int l1, int64_t bc) {
+  int n = 0;
+  for (int l = l0; l < l1; ++l) n += affd_T_grouped(s, l);
+  std::vector<int> fl;
+  for (int l = l0; l < l1; ++l)
+    if (affd_F_grouped(s, l, bc, n)) fl.push_back(l);
+  return fl;
 }
 
 AffdTTGroup affd_T_group(const sk_sketch *s, int l0, int l1, int64_t bc, void *const *out, const void *const *theta0) {

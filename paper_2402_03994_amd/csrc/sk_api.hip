@@ -823,9 +823,7 @@ int sketch_apply(sk_sketch *s, const void *const *grads, sk_dtype dtype, int64_t
         // layers that go through the grouped passes in a call of this size (those that do not fit the workspace
         // stay with the paths below)
         std::vector<char> done(l1 - l0, 0);
-        std::vector<int> fl;
-        for (int l = l0; l < l1; ++l)
-          if (affd_F_grouped(s, l, bc)) fl.push_back(l);
+        const std::vector<int> fl = affd_F_layers(s, l0, l1, bc);
         for (size_t i = 0; i < fl.size();) {
           int nl = 0;
           const AffdTTGroup g = affd_F_group(s, fl.data() + i, (int)(fl.size() - i), l0, bc, grads, &nl);

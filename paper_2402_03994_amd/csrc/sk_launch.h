@@ -201,8 +201,8 @@ AffdTTGroup affd_T_group(const sk_sketch *s, int l0, int l1, int64_t bc, void *c
 // phases: bit 0 = z to W, bit 1 = the outputs
 void run_affd_T(const sk_sketch *s, const AffdTTGroup &g, const float *z, int64_t b_begin, int64_t bc, int out_dtype,
                 int phases, hipStream_t st);
-// Does the layer take the passes of sk_affd_tt.hip forward, in a call of bc vectors?
-bool affd_F_grouped(const sk_sketch *s, int layer, int64_t bc);
+// The layers of a call of bc vectors that take the passes of sk_affd_tt.hip forward.
+std::vector<int> affd_F_layers(const sk_sketch *s, int l0, int l1, int64_t bc);
 // The forward by those passes: entries (layer, run of slabs) of the first *taken listed layers (inputs x from layer
 // l0 on, held in `out`), as many as fit the workspace.  Phases: bit 0 = rows, bit 1 = columns; G^T of entry i is at
 // u_off[i], for run_affd_transposed_outm.

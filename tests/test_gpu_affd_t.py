@@ -121,3 +121,20 @@ def test_affd_vector_turns(n, batch, dev):  # noqa: F811
     for o, r in zip(outs, refs):
         assert rel_err(o.cpu().numpy(), r) < TOL_F32
     s.close()
+
+
+# Which calls of up to three vectors take the grouped passes: a lone layer of one slab up to D below 2^20 values, none of
+# several, layers of seven slabs with two vectors and not with three, several-slab and small layers side by side.
+@pytest.mark.parametrize("D,shapes,batches", [(16384, [(1, 2 ** 21 + 9)], (1, 3)), (1 << 19, [(1, 2 ** 20 - 7)], (1, 2)),
+                                              (4096, [(1, 7 * 2 ** 20 - 3), (1, 6 * 2 ** 20 + 1)], (2, 3)),
+                                              (1 << 20, [(1, 2 ** 20 - 7), (1, 9)], (1, 2, 3)),
+                                              (16384, [(1, 2 ** 22 - 3), (1, 768), (1, 12 * 2 ** 20)], (3,))])
+def test_affd_few_vectors_routes(D, shapes, batches, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    s = Sketch("affd", shapes, D, 41, device=dev)
+    for batch in batches:
+        xs = rand_inputs(shapes, batch, 42)
+        ref = O.apply("affd", shapes, D, 41, [x.numpy() for x in xs])
+        y = s.apply([x.to(dev) for x in xs])
+        assert rel_err(y.cpu().numpy(), ref) < TOL_F32
+    s.close()
