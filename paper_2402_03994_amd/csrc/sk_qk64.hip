@@ -409,6 +409,51 @@ __device__ __forceinline__ void qk64_outer(const Qk64Outer &t, int bm, int64_t b
     }
 }
 
+// Thin outputs of transposes (outer_thin): a thread per output and VB vectors,
+// the factor's entry read once for them, sums in the order of k as above.
+template <int VB>
+__global__ __launch_bounds__(256) void k_qk64_thin(Qk64OuterArgs a) {
+  const uint32_t blk = a.base + blockIdx.x;
+  int ti = 0;
+  while (ti + 1 < a.n && blk >= a.blk0[ti + 1]) ++ti;
+  const Qk64Outer &t = a.t[ti];
+  const uint32_t e = blk - a.blk0[ti], nb = (uint32_t)t.nbn;
+  const int64_t at = (int64_t)(e % nb) * 256 + threadIdx.x;
+  if (at >= (int64_t)t.M * t.N) return;
+  const int64_t i = at / t.N, j = at - i * t.N, v0 = (int64_t)(e / nb) * VB;
+  const bool qs = t.qvs == 0;  // the factor is Q
+  const float *f = qs ? (const float *)t.q + j : t.p + i * t.psi;
+  const int64_t fstep = qs ? t.N : t.psk, step = qs ? t.psk : t.N;
+  const float *x[VB];
+  double y[VB];
+#pragma unroll
+  for (int u = 0; u < VB; ++u) {
+    const int64_t v = min(v0 + u, a.nv - 1);
+    x[u] = qs ? t.p + v * t.pvs + i * t.psi : (const float *)t.q + v * t.qvs + j;
+    y[u] = 0.0;
+  }
+#pragma unroll 8
+  for (int k = 0; k < (int)t.K; ++k) {
+    const double fv = (double)*f;
+    f += fstep;
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
+      y[u] += (double)*x[u] * fv;
+      x[u] += step;
+    }
+  }
+  const double th = t.theta ? (double)t.theta[at] : 0.0;
+#pragma unroll
+  for (int u = 0; u < VB; ++u) {
+    if (v0 + u >= a.nv) break;
+    const float o = (float)(y[u] + th);
+    if (a.out_bf16)
+      ((uint16_t *)t.o)[(v0 + u) * t.ovs + at] = f2bf(o);
+    else
+      ((float *)t.o)[(v0 + u) * t.ovs + at] = o;
+  }
+}
+
 template <bool KS, bool QB>
 __global__ __launch_bounds__(256, 3) void k_qk64_outer(Qk64OuterArgs a) {
   __shared__ double red[KS ? 2 : 1][8][4][64];
@@ -442,8 +487,8 @@ namespace {
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Workgroup numbers of a group stay below 2^32 (a call's chunks have at most 2^20 vectors, and a workgroup writes 64
-// bytes or more of a matrix of more than one), but not its threads: a one-row or one-column matrix makes a workgroup of
-// every 64 or 32 values, and nine of 2^19 entries with 256 vectors are 2^32 threads.
+// bytes or more of a matrix of more than one), but not its threads: a matrix of few columns makes a workgroup of
+// every 32 rows, and eight of 2^19 rows with 256 vectors are 2^33 threads.
 void launch_dot(Qk64DotArgs &a, bool qb, hipStream_t st) {
   int64_t blk = 0;
   for (int i = 0; i < a.n; ++i) {
@@ -480,6 +525,44 @@ void launch_outer(Qk64OuterArgs &a, bool qb, hipStream_t st) {
       hipLaunchKernelGGL((k_qk64_outer<KS, true>), dim3(count), dim3(256), 0, st, a);
     else
       hipLaunchKernelGGL((k_qk64_outer<KS, false>), dim3(count), dim3(256), 0, st, a);
+  });
+}
+
+// Fewer rows than 16, columns than 64 or terms than 16 leave matrix-core tiles padded, and a factor of one or few rows
+// then takes longer than a thread per output.  In ns of the whole device, by the slopes of 64 vectors: a thread per output
+// (K + 7) / 4000 each (a factor entry read for every vector: more than twice that), a tile of 16 x 64 one and one more for every 16 terms, half
+// as much again where three of the workgroup's waves have no rows.  64 vectors, tiles / threads: a 1 x 40000 matrix (1, 64) 167 /
+// 37 us, 40000 x 1 449 / 37, 8 x 40000 (4, 64) 265 / 157, 16 x 40000 (4, 8) 205 / 110, 768 x 768 (3, 3) 59 / 72.
+bool outer_thin(const Qk64Outer &t, int vb) {
+  const double tiles = (double)cdiv(t.M, 16) * (double)cdiv(t.N, 64) * (t.M <= 16 ? 1.5 : 1.0);
+  return (vb == 4 ? 0.25e-3 : 0.6e-3) * t.M * t.N * (double)(t.K + 7) < tiles * (double)(1 + cdiv(t.K, 16));
+}
+
+// Transposes (fp32 operands): thin outputs by k_qk64_thin.
+void launch_outer_T(const Qk64OuterArgs &a, hipStream_t st) {
+  Qk64OuterArgs wide{}, thin{};
+  wide.nv = thin.nv = a.nv;
+  wide.out_bf16 = thin.out_bf16 = a.out_bf16;
+  const int vb = a.nv >= 4 ? 4 : 1;
+  int64_t blk = 0;
+  for (int i = 0; i < a.n; ++i) {
+    if (!outer_thin(a.t[i], vb)) {
+      wide.t[wide.n++] = a.t[i];
+      continue;
+    }
+    Qk64Outer &t = thin.t[thin.n];
+    t = a.t[i];
+    t.nbn = (int)cdiv((int64_t)t.M * t.N, 256);
+    thin.blk0[thin.n++] = (uint32_t)blk;
+    blk += t.nbn * cdiv(a.nv, vb);
+  }
+  launch_outer<false>(wide, false, st);
+  grid_parts(blk, [&](uint32_t first, uint32_t count) {
+    thin.base = first;
+    if (vb == 4)
+      hipLaunchKernelGGL(k_qk64_thin<4>, dim3(count), dim3(256), 0, st, thin);
+    else
+      hipLaunchKernelGGL(k_qk64_thin<1>, dim3(count), dim3(256), 0, st, thin);
   });
 }
 
@@ -673,8 +756,8 @@ void launch_qk64_T(const sk_sketch *s, const Qk64Group &g, const float *z, int64
     u.M = ld.m;
     u.N = ld.nc;
   }
-  launch_outer<false>(a, false, st);
-  launch_outer<false>(b, false, st);
+  launch_outer_T(a, st);
+  launch_outer_T(b, st);
 }
 
 }  // namespace sk

@@ -52,7 +52,7 @@ def test_qk_fp64_sums(name, batch, ws_mb, dtype, dev, monkeypatch):  # noqa: F81
     s.close()
 
 
-# 18.9 million workgroups of 64 outputs (more than one launch takes): every vector is the first one times a power of two
+# One-row matrices of many vectors: every vector is the first one times a power of two
 def test_qk_thin_transpose(dev):  # noqa: F811
     from paper_2402_03994_amd import Sketch
     shapes, batch, seed = [(1, 2 ** 19, 1, 1)] * 9, 256, 6
@@ -65,4 +65,41 @@ def test_qk_thin_transpose(dev):  # noqa: F811
     for o, r in zip(outs, refs):
         assert rel_err(o[:1].cpu().numpy(), r) < TOL
         assert torch.equal(o, o[:1] * p2.to(dev)[:, None])
+    s.close()
+
+
+# More workgroups of 32 rows than one launch takes (8 layers to a group: 33 million), forward
+def test_qk_many_workgroups(dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    shapes, batch, seed = [(2 ** 19, 4, 4, 1)] * 9, 256, 6
+    s = Sketch("qk", shapes, 36, seed, device=dev)
+    x0 = rand_inputs(shapes[:1], 1, seed, dtype=torch.bfloat16)[0]
+    p2 = (2.0 ** (torch.arange(batch) % 7)).to(dev)
+    x = x0.to(dev) * p2.to(torch.bfloat16)[:, None]
+    y = s.apply([x] * 9)
+    ref = O.apply("qk", shapes, 36, seed, [oracle_in(x0)[0]] * 9, dtype="bf16")
+    assert rel_err(y[:1].cpu().numpy(), ref) < TOL
+    assert torch.equal(y, y[:1] * p2[:, None])
+    s.close()
+
+
+# Transposes with thin outputs (a thread per output) beside layers on the matrix cores: one and few rows and columns,
+# short and long sums, one vector and groups of four with a rest
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("batch", [1, 4, 7])
+def test_qk_thin_outputs(batch, dtype, dev):  # noqa: F811
+    from paper_2402_03994_amd import Sketch
+    shapes = [(1, 4099, 1, 64), (4099, 1, 64, 1), (96, 130, 40, 33), (3, 1027, 2, 20), (1027, 5, 33, 3), (12, 700, 4, 64),
+              (700, 24, 8, 4), (257, 255, 3, 3), (160, 192, 48, 64)]
+    D, seed = sum(s[2] * s[3] for s in shapes), 8
+    s = Sketch("qk", shapes, D, seed, device=dev)
+    g = torch.Generator().manual_seed(seed)
+    z = torch.randn((batch, D), generator=g)
+    th = [torch.randn(r * c, generator=g) * 0.02 if i % 2 else None for i, (r, c, _, _) in enumerate(shapes)]
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    outs = s.apply_T(z.to(dev), out_dtype=tdt, theta0=[None if t is None else t.to(dev) for t in th])
+    refs = O.apply_T("qk", shapes, D, seed, z.numpy().astype(np.float64),
+                     theta0=[None if t is None else t.numpy() for t in th])
+    for o, r in zip(outs, refs):
+        assert rel_err(o.float().cpu().numpy(), r) < (TOL_BF16 if dtype == "bf16" else TOL)
     s.close()
